@@ -2,8 +2,7 @@
 // advanced together.  Per SSP-RK3 step: one launch for the dt of every
 // instance (plus its per-instance finish), then per stage either
 //   - one launch (AF_BATCH_FUSED) over the point tiles of all instances
-//     (two 16 x 16 tiles per 512-thread workgroup) and their cell tiles,
-//     which compute their own nine-point sources so that nothing in the
+//     and their cell tiles (512 threads each), which compute their own nine-point sources so that nothing in the
 //     launch waits on anything, or
 //   - one launch of the point update over the (instance, tile) work items
 //     of all instances and one launch of the cell update over theirs, with
@@ -30,6 +29,7 @@
 
 #include "af_device.h"
 #include "af_mhd.h"
+#include "af_points.h"
 #include "af_tiles.h"
 
 using namespace afm;
@@ -46,6 +46,7 @@ struct BInst {          // one instance in one launch of one stage
   CState u;             // stage input U^(k)
   CState un;            // U^n (read when a_k != 0)
   MState out;           // stage output
+  MState stash;         // out, or a scratch state where the output is U^n (see points_tile)
   double* src;          // nine-point sources of U^(k)'s cells
   const double* dt;     // the instance's time step (device)
   int first;            // first work item of the instance in this launch
@@ -98,9 +99,9 @@ __device__ __forceinline__ bool item_range(int items, int& first, int& end, int&
 inline int flat_grid(int items) { return NXCD * ((items + NXCD - 1) / NXCD); }
 
 template <class R, bool PERSIST>
-__global__ __launch_bounds__(PNT, 2) void kb_points(const BInst* __restrict__ I, int n,
-                                                                          int items, double ca, double cb,
-                                                                          Counters* cn) {
+__global__ __launch_bounds__(point_threads<R>(), point_waves<R>()) void kb_points(const BInst* __restrict__ I, int n,
+                                                                                 int items, double ca, double cb,
+                                                                                 Counters* cn) {
   __shared__ R s[point_fields<R>()][PB][PB];
   int it, end, step;
   if (!item_range<PERSIST>(items, it, end, step)) return;
@@ -109,7 +110,8 @@ __global__ __launch_bounds__(PNT, 2) void kb_points(const BInst* __restrict__ I,
     const Geo g = I[m].g;
     const int t = it - I[m].first, ntx = I[m].ntx;
     __syncthreads();  // the previous item's LDS reads are done
-    points_tile<R>(g, I[m].u, I[m].un, I[m].out, I[m].src, *I[m].dt, ca, cb, cn, t % ntx, t / ntx, s);
+    points_tile<R>(g, I[m].u, I[m].un, I[m].out, I[m].stash, I[m].src, *I[m].dt, ca, cb, cn, t % ntx, t / ntx, s,
+                   nullptr);
   }
 }
 
@@ -132,16 +134,18 @@ __global__ __launch_bounds__(CBX * CBY) void kb_cells(const BInst* __restrict__ 
 }
 
 // One stage of every instance in one launch (AF_BATCH_FUSED): workgroups
-// [0, npairs) take pairs of point tiles (tiles 2q and 2q+1 of the batch's
-// point list, run side by side by the two halves of the 512-thread
-// workgroup; an odd last tile leaves the second half recomputing the first
-// half's tile without storing anything), workgroups [npairs, npairs +
-// citems) cell tiles.  The two kinds share nothing within the stage: the
+// [0, npts) take the point tiles of the batch's point list -- for the FP64
+// stage one each, for the FP32-bulk stage (256 threads a tile) tiles 2q and
+// 2q+1, run side by side by the two halves of the 512-thread workgroup; an odd
+// last tile leaves the second half recomputing the first half's tile without
+// storing anything -- and workgroups [npts, npts + citems) cell tiles.  The
+// two kinds share nothing within the stage: the
 // cell tiles compute their cells' nine-point sources themselves, from the
 // stage input, instead of reading the point tiles' (which would make a cell
 // tile wait for its neighbours' point tiles), so the launch has no
 // inter-workgroup synchronisation at all.
 constexpr int FUSED_THREADS = 512;
+template <class R> constexpr int fused_tiles() { return FUSED_THREADS / point_threads<R>(); }
 
 template <class R, int CBX, int CBY>
 __global__ __launch_bounds__(FUSED_THREADS) void kb_stage(const BInst* __restrict__ P, const BInst* __restrict__ C,
@@ -149,26 +153,31 @@ __global__ __launch_bounds__(FUSED_THREADS) void kb_stage(const BInst* __restric
                                                           Counters* cn) {
   static_assert(CBX * CBY == FUSED_THREADS, "one cell tile per workgroup");
   union Lds {
-    R pts[2][point_fields<R>()][PB][PB];
+    R pts[fused_tiles<R>()][point_fields<R>()][PB][PB];
     CellsLDS<R, CBX, CBY> cells;
   };
   __shared__ Lds L;
   const int tid = (int)(threadIdx.y * blockDim.x + threadIdx.x);
-  const int npairs = (pitems + 1) / 2;
+  constexpr int PER = fused_tiles<R>();
+  const int npts = (pitems + PER - 1) / PER;
   const int it = (int)blockIdx.x;
-  if (it < npairs) {
-    const int half = tid / PNT, ltid = tid % PNT;
-    const int t0 = 2 * it + half;
+  if (it < npts) {
+    const int half = PER == 2 ? tid / point_threads<R>() : 0, ltid = PER == 2 ? tid % point_threads<R>() : tid;
+    const int t0 = PER * it + half;
     const bool live = t0 < pitems;
-    const int t = live ? t0 : 2 * it;
+    const int t = live ? t0 : PER * it;
     const int m = find_inst(P, n, t);
     const Geo g = P[m].g;
     const int tt = t - P[m].first, ntx = P[m].ntx;
-    points_tile_lean<R>(g, P[m].u, P[m].un, P[m].out, nullptr, *P[m].dt, ca, cb, cn, tt % ntx, tt / ntx,
-                        L.pts[half], nullptr, ltid % PB, ltid / PB, live);
+    if constexpr (PER == 2)
+      points_tile_f32<R>(g, P[m].u, P[m].un, P[m].out, nullptr, *P[m].dt, ca, cb, cn, tt % ntx, tt / ntx,
+                         L.pts[half], nullptr, ltid % PB, ltid / PB, live);
+    else
+      fp64::points_tile(g, P[m].u, P[m].un, P[m].out, P[m].stash, nullptr, *P[m].dt, ca, cb, cn, tt % ntx, tt / ntx,
+                        L.pts[0], nullptr, ltid);
     return;
   }
-  const int c = it - npairs;
+  const int c = it - npts;
   if (c >= citems) return;
   const int m = find_inst(C, n, c);
   const int t = c - C[m].first, ntx = C[m].ntx;
@@ -241,14 +250,14 @@ void launch_cells(bool persist, int shape, int grid, hipStream_t s, const BInst*
 template <class R>
 void launch_points(bool persist, int grid, hipStream_t s, const BInst* I, int n, int items, double ca, double cb,
                    Counters* cn) {
-  if (persist) kb_points<R, true><<<grid, dim3(PB, PB), 0, s>>>(I, n, items, ca, cb, cn);
-  else kb_points<R, false><<<flat_grid(items), dim3(PB, PB), 0, s>>>(I, n, items, ca, cb, cn);
+  if (persist) kb_points<R, true><<<grid, point_threads<R>(), 0, s>>>(I, n, items, ca, cb, cn);
+  else kb_points<R, false><<<flat_grid(items), point_threads<R>(), 0, s>>>(I, n, items, ca, cb, cn);
 }
 
 template <class R>
 void launch_fused(int shape, hipStream_t s, const BInst* P, const BInst* C, int n, int pitems, int citems,
                   double ca, double cb, Counters* cn) {
-  const int grid = (pitems + 1) / 2 + citems;  // one work item per workgroup
+  const int grid = (pitems + fused_tiles<R>() - 1) / fused_tiles<R>() + citems;
   if (shape == 0) kb_stage<R, 32, 16><<<grid, dim3(32, 16), 0, s>>>(P, C, n, pitems, citems, ca, cb, cn);
   else kb_stage<R, 16, 32><<<grid, dim3(32, 16), 0, s>>>(P, C, n, pitems, citems, ca, cb, cn);
 }
@@ -424,6 +433,7 @@ int build_tables(af_mhd_batch* b) {
       r.u = CState{in.cell, in.xface, in.yface, in.vert};
       r.un = CState{U.cell, U.xface, U.yface, U.vert};
       r.out = MState{out.cell, out.xface, out.yface, out.vert};
+      r.stash = k < 2 ? r.out : MState{b->s1[m].cell, b->s1[m].xface, b->s1[m].yface, b->s1[m].vert};
       r.src = b->src[m];
       r.dt = b->dt + m;
       r.first = cfirst;
@@ -441,6 +451,7 @@ int build_tables(af_mhd_batch* b) {
       r.u = CState{in.cell, in.xface, in.yface, in.vert};
       r.un = CState{U.cell, U.xface, U.yface, U.vert};
       r.out = MState{out.cell, out.xface, out.yface, out.vert};
+      r.stash = k < 2 ? r.out : MState{b->s1[m].cell, b->s1[m].xface, b->s1[m].yface, b->s1[m].vert};
       r.src = b->src[m];
       r.dt = b->dt + m;
       r.first = pfirst;
@@ -543,6 +554,7 @@ int tune_instance(af_mhd_batch* b, int m, double us[NSHAPE]) {
   r.u = CState{U.cell, U.xface, U.yface, U.vert};
   r.un = r.u;
   r.out = MState{b->s1[m].cell, b->s1[m].xface, b->s1[m].yface, b->s1[m].vert};
+  r.stash = r.out;
   r.src = b->src[m];
   r.dt = b->dt + m;
   hipStream_t s = b->stream;
@@ -666,8 +678,9 @@ int af_mhd_batch_init(const af_mhd_params* p, int n, const af_mhd_state* states,
     b->user.push_back(states[m]);
   }
   batch_layout(p, n, static_cast<char*>(workspace_dev), b);
-  b->grid_points = b->f32 ? persistent_grid(reinterpret_cast<const void*>(&kb_points<float, true>), PNT)
-                          : persistent_grid(reinterpret_cast<const void*>(&kb_points<double, true>), PNT);
+  b->grid_points = b->f32 ? persistent_grid(reinterpret_cast<const void*>(&kb_points<float, true>), point_threads<float>())
+                          : persistent_grid(reinterpret_cast<const void*>(&kb_points<double, true>),
+                                            point_threads<double>());
   b->grid_cells = persistent_grid(b->f32 ? cells_fn<float>(0) : cells_fn<double>(0), 512);  // 512 threads either shape
   b->grid_dt = persistent_grid(reinterpret_cast<const void*>(&kb_dt_partial), BLK);
   (void)hipGetLastError();

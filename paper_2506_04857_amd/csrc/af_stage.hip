@@ -24,6 +24,7 @@
 #include <string>
 
 #include "af_device.h"
+#include "af_points.h"
 #include "af_tiles.h"
 #include "af_mhd.h"
 
@@ -50,17 +51,16 @@ inline int cells_tiles_y(const Geo& g) { return (g.ny + CBY0 - 4) / (CBY0 - 3); 
 // workgroups store 0).
 // WDT: a step's last stage, whose epilogue also writes the wave-speed maxima.
 template <class R, bool WDT>
-__global__ __launch_bounds__(PNT, 2) void k_points(Geo g, CState u, CState un, MState out,
-                                                   double* __restrict__ src, const double* dtp, double ca,
-                                                   double cb, Counters* cn, int ntx, int nty,
-                                                   double* __restrict__ wpart) {
+__global__ __launch_bounds__(point_threads<R>(), point_waves<R>()) void k_points(
+    Geo g, CState u, CState un, MState out, MState stash, double* __restrict__ src, const double* dtp, double ca,
+    double cb, Counters* cn, int ntx, int nty, double* __restrict__ wpart) {
   __shared__ R s[point_fields<R>()][PB][PB];
   int bx, by;
   if (!xcd_tile(ntx, nty, bx, by)) {
-    if (WDT && threadIdx.x == 0 && threadIdx.y == 0) wpart[blockIdx.x] = 0.0;
+    if (WDT && threadIdx.x == 0) wpart[blockIdx.x] = 0.0;
     return;
   }
-  points_tile<R>(g, u, un, out, src, *dtp, ca, cb, cn, bx, by, s, WDT ? wpart + blockIdx.x : nullptr);
+  points_tile<R>(g, u, un, out, stash, src, *dtp, ca, cb, cn, bx, by, s, WDT ? wpart + blockIdx.x : nullptr);
 }
 
 template <class R, bool WDT>
@@ -426,6 +426,12 @@ int run_stage(af_mhd_ctx* c, int k, const af_mhd_state* un, const af_mhd_state* 
   const CState u = cstate(uk);
   const CState n = cstate(k == 0 ? uk : un);  // not read when a_k = 0
   const MState o{out->cell, out->xface, out->yface, out->vert};
+  // points may hold an intermediate value at their place of the output until
+  // they are written; where the output is U^n itself, at their place of the
+  // first scratch state, which no stage in place reads (af_mhd_step's last
+  // stage has its input in the second)
+  double* const* sc = c->ws.scratch[0];
+  const MState st{o.a, o.x == n.x ? sc[1] : o.x, o.y == n.y ? sc[2] : o.y, o.v == n.v ? sc[3] : o.v};
   const int ptx = points_tiles_x(g), pty = points_tiles_y(g);
   double* const wcells = wpart ? wpart + xcd_grid(ptx, pty) : nullptr;
   hipEvent_t end;
@@ -433,11 +439,11 @@ int run_stage(af_mhd_ctx* c, int k, const af_mhd_state* un, const af_mhd_state* 
   if (e != hipSuccess) return fail(c, AF_EHIP, hipGetErrorString(e));
   {
     if (c->f32)
-      (wpart ? k_points<float, true> : k_points<float, false>)<<<xcd_grid(ptx, pty), dim3(PB, PB), 0, s>>>(
-          g, u, n, o, c->ws.src, dt_dev, A[k], B[k], c->ws.cnt, ptx, pty, wpart);
+      (wpart ? k_points<float, true> : k_points<float, false>)<<<xcd_grid(ptx, pty), point_threads<float>(), 0, s>>>(
+          g, u, n, o, st, c->ws.src, dt_dev, A[k], B[k], c->ws.cnt, ptx, pty, wpart);
     else
-      (wpart ? k_points<double, true> : k_points<double, false>)<<<xcd_grid(ptx, pty), dim3(PB, PB), 0, s>>>(
-          g, u, n, o, c->ws.src, dt_dev, A[k], B[k], c->ws.cnt, ptx, pty, wpart);
+      (wpart ? k_points<double, true> : k_points<double, false>)<<<xcd_grid(ptx, pty), point_threads<double>(), 0, s>>>(
+          g, u, n, o, st, c->ws.src, dt_dev, A[k], B[k], c->ws.cnt, ptx, pty, wpart);
   }
   e = timer_end(c, end);
   if (e == hipSuccess) e = timer_begin(c, KernelTimer::CELLS, &end);

@@ -1,8 +1,9 @@
 // af_tiles.h -- the tile bodies of one SSP-RK3 stage of the PP Active Flux
-// scheme for 2D ideal MHD with the Godunov-Powell source (gfx950): the point
-// update (points_tile) and the cell update (cells_tile), the XCD-aware tile
-// order and the reduction helpers.  Shared by the single-grid kernels
-// (af_stage.hip) and the persistent batched kernels (af_batch.hip).
+// scheme for 2D ideal MHD with the Godunov-Powell source (gfx950): the
+// FP32-bulk point update (points_tile; the FP64 one is in af_points.h) and
+// the cell update (cells_tile), the XCD-aware tile order and the reduction
+// helpers.  Shared by the single-grid kernels (af_stage.hip) and the batched
+// kernels (af_batch.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -117,7 +118,7 @@ __device__ __forceinline__ void source_nine(BF Bat, PF Psiat, R rdx, R rdy, R S[
 // ------------------------------------------------------- fused point update
 // One launch updates the point values V, X, Y owned by a tile of
 // (PB-2) x (PB-2) cells (cell (i,j) owns V(i,j), X(i,j), Y(i,j)); the
-// PB x PB threads cover the tile plus a one-cell ring.  The point-value
+// tile's PB x PB places cover it plus a one-cell ring.  The point-value
 // stencils of Section 2.3 run along four families of lines of the
 // half-spaced lattice:
 //   a  horizontal lines through V and Y  (V: FVS in x; Y: central in x)
@@ -131,7 +132,7 @@ __device__ __forceinline__ void source_nine(BF Bat, PF Psiat, R rdx, R rdy, R S[
 // Central direction: R = (F(up) - F(dn))/h, div part (B(up) - B(dn))/h.
 // The first-order LLF state uses the four neighbours of the point (the
 // line neighbours at +-h for FVS directions, at +-h/2 for the central one).
-constexpr int PB = 16, PNT = PB * PB;
+constexpr int PB = 16;
 constexpr int RF = 12;  // exchange fields of the cell tile: record (4) + LLF flux (8)
 
 // Point accumulators: high-order RHS h = -R_x - R_y with the div part, and
@@ -161,18 +162,10 @@ __device__ __forceinline__ void finish(const Geo& g, double dt, const double U0[
   double UH[NV], UL[NV], W[NV];
   R Ps[NV];
   psi(U0, Ps);
-  if constexpr (IsF32<R>::value) {
 #pragma unroll
-    for (int c = 0; c < NV; ++c) {
-      UH[c] = U0[c] + dt * (double)(P.h[c] - P.divh * Ps[c]);
-      UL[c] = U0[c] + (double)(P.l[c] - (float)dt * P.divl * Ps[c]);
-    }
-  } else {
-#pragma unroll
-    for (int c = 0; c < NV; ++c) {
-      UH[c] = U0[c] + dt * (P.h[c] - P.divh * Ps[c]);
-      UL[c] = U0[c] + P.l[c] - dt * P.divl * Ps[c];
-    }
+  for (int c = 0; c < NV; ++c) {
+    UH[c] = U0[c] + dt * (double)(P.h[c] - P.divh * Ps[c]);
+    UL[c] = U0[c] + (double)(P.l[c] - (float)dt * P.divl * Ps[c]);
   }
   if (!in_G_fast(UL)) count(&cn->n_llf_not_admissible);
   limit_point(UH, UL, g.gm1, W, cn, true);
@@ -191,7 +184,7 @@ __device__ __forceinline__ int clamp_pt(int i, int np) { return i < -1 ? -1 : (i
 
 // LDS layout (fields of PB x PB values of the compute type): states of the
 // tile's V, X, Y and centre values, then the records of the line family in
-// flight (see points_tile_lean).
+// flight (see points_tile_f32).
 constexpr int SV_ = 0, SX_ = 8, SY_ = 16, SC_ = 24;
 template <class R>
 constexpr int point_fields() { return 40; }
@@ -207,23 +200,20 @@ __device__ __forceinline__ void sts8(R (*s)[PB][PB], int base, int ty, int tx, c
   for (int c = 0; c < NV; ++c) s[base + c][ty][tx] = (R)U[c];
 }
 
-// ---------------------------------- point tile with rebuilt evaluations
-// LDS holds the tile's V, X, Y and centre states (32 fields of the compute
-// type R) and, for the one line family in flight, the record
-// (1/rho, p, c_f, sqrt(rho)) of its two point types (8 fields): 40 x PB x PB
-// values, 80 KB for the FP64 stage (two workgroups per CU), 40 KB for the
-// FP32-bulk one.  A point's flux, v_n and spectral radius in the family's
-// direction are rebuilt from its state and record with the operations of
-// eval_dir (for FP64 bit for bit).  The families run in the order b, c, a,
-// d, which keeps at most two point accumulators live: b's records are
-// formed from the values the tile load brings and its line sums share the
-// centre-value phase (they read no centre value); c, a and d each take a
-// barrier pair (records, then line sums).  A point is finished (limiter,
-// SSP combination, store) after the next family's records, its U^n loaded
-// just before them.
-// FP32-bulk: states and records in FP32; a thread's own FP64 states (for the
-// records, whose pressure recovery is FP64, and for the finish) and its FP64
-// centre value stay in registers from the tile load.
+// ------------------------------------ point tile of the FP32-bulk stage
+// 256 threads, one per place (R = float).  LDS holds the tile's V, X, Y and
+// centre states in FP32 (32 fields) and, for the one line family in flight,
+// the record (1/rho, p, c_f, sqrt(rho)) of its two point types (8 fields):
+// 40 x PB x PB values, 40 KB.  A point's flux, v_n and spectral radius in the
+// family's direction are rebuilt from its state and record.  The families run
+// in the order b, c, a, d, which keeps at most two point accumulators live:
+// b's records are formed from the values the tile load brings and its line
+// sums share the centre-value phase (they read no centre value); c, a and d
+// each take a barrier pair (records, then line sums).  A point is finished
+// (limiter, SSP combination, store) after the next family's records, its U^n
+// loaded just before them.  A thread's own FP64 states (for the records, whose
+// pressure recovery is FP64, and for the finish) and its FP64 centre value
+// stay in registers from the tile load.
 constexpr int LQ0 = 32, LQ1 = 36;
 
 // Flux of a state held in any type S (the FP64 stage: S = R = double, the
@@ -428,11 +418,10 @@ __device__ __forceinline__ void lean_fvs(R (*s)[PB][PB], int dir, int so, int sb
 // arithmetic and barriers but stores nothing and counts nothing (a
 // workgroup that runs two tiles side by side and has only one to do).
 template <class R>
-__device__ __forceinline__ void points_tile_lean(const Geo& g, CState u, CState un, MState out,
+__device__ __forceinline__ void points_tile_f32(const Geo& g, CState u, CState un, MState out,
                                                  double* __restrict__ src, double dt, double ca, double cb,
                                                  Counters* cn, int bx, int by, R (*s)[PB][PB],
                                                  double* __restrict__ wslot, int tx, int ty, bool live) {
-  constexpr bool F32 = IsF32<R>::value;
   double wm = 0.0;
   double* const wmax = wslot ? &wm : nullptr;
   const int i0 = bx * (PB - 2) - 1, j0 = by * (PB - 2) - 1;
@@ -445,39 +434,23 @@ __device__ __forceinline__ void points_tile_lean(const Geo& g, CState u, CState 
   const R rdx = (R)g.rdx, rdy = (R)g.rdy, lxr = (R)lx, lyr = (R)ly;
   const int txl = tx > 0 ? tx - 1 : tx, txr = tx < PB - 1 ? tx + 1 : tx;
   const int tyd = ty > 0 ? ty - 1 : ty, tyu = ty < PB - 1 ? ty + 1 : ty;
-  // a thread's own FP64 states of type 0 V, 1 X, 2 Y: from LDS for the
-  // FP64 stage; kept in registers from the tile load for the FP32-bulk one
-  // (whose LDS holds FP32)
-  double oV[F32 ? NV : 1], oX[F32 ? NV : 1], oY[F32 ? NV : 1];
+  // a thread's own FP64 states of type 0 V, 1 X, 2 Y, kept in registers from
+  // the tile load (LDS holds FP32)
+  double oV[NV], oX[NV], oY[NV];
   auto own = [&](int which, double U[NV]) {
-    if constexpr (F32) {
 #pragma unroll
-      for (int c = 0; c < NV; ++c) U[c] = which == 0 ? oV[c] : which == 1 ? oX[c] : oY[c];
-    } else {
-      lds8(s, which == 0 ? SV_ : which == 1 ? SX_ : SY_, ty, tx, U);
-    }
+    for (int c = 0; c < NV; ++c) U[c] = which == 0 ? oV[c] : which == 1 ? oX[c] : oY[c];
   };
 
   // 0: the tile's raw point values into LDS, and the records of family b
   //    (below) of the thread's own V and X, from the values loaded
-  if constexpr (F32) {
-    ldV(g, u.v, i, j, oV);
-    sts8(s, SV_, ty, tx, oV);
-    ldX(g, u.x, i, j, oX);
-    sts8(s, SX_, ty, tx, oX);
-    ldY(g, u.y, i, j, oY);
-    sts8(s, SY_, ty, tx, oY);
-    lean_records(s, g, ty, tx, oV, oX, 1);
-  } else {
-    double wv[NV], wx[NV], w[NV];
-    ldV(g, u.v, i, j, wv);
-    ldX(g, u.x, i, j, wx);
-    ldY(g, u.y, i, j, w);
-    sts8(s, SV_, ty, tx, wv);
-    sts8(s, SX_, ty, tx, wx);
-    sts8(s, SY_, ty, tx, w);
-    lean_records(s, g, ty, tx, wv, wx, 1);
-  }
+  ldV(g, u.v, i, j, oV);
+  sts8(s, SV_, ty, tx, oV);
+  ldX(g, u.x, i, j, oX);
+  sts8(s, SX_, ty, tx, oX);
+  ldY(g, u.y, i, j, oY);
+  sts8(s, SY_, ty, tx, oY);
+  lean_records(s, g, ty, tx, oV, oX, 1);
   // the cell average of the centre value, in flight during family b
   double A[NV];
   ldA(g, u.a, i, j, A);
@@ -499,38 +472,21 @@ __device__ __forceinline__ void points_tile_lean(const Geo& g, CState u, CState 
   double C[NV];
   {
     double Uc[NV], f[NV], w[NV], q[NV];
-    if constexpr (F32) {
 #pragma unroll
-      for (int c = 0; c < NV; ++c) f[c] = oX[c];
-      ldX(g, u.x, i + 1, j, w);
+    for (int c = 0; c < NV; ++c) f[c] = oX[c];
+    ldX(g, u.x, i + 1, j, w);
 #pragma unroll
-      for (int c = 0; c < NV; ++c) Uc[c] = oY[c];
-      ldY(g, u.y, i, j + 1, q);
-    } else {
-      lds8(s, SX_, ty, tx, f);
-      lds8(s, SX_, ty, txr, w);
-      lds8(s, SY_, ty, tx, Uc);
-      lds8(s, SY_, tyu, tx, q);
-    }
+    for (int c = 0; c < NV; ++c) Uc[c] = oY[c];
+    ldY(g, u.y, i, j + 1, q);
 #pragma unroll
     for (int c = 0; c < NV; ++c) f[c] = -4.0 * ((f[c] + w[c]) + (Uc[c] + q[c]));
-    if constexpr (F32) {
 #pragma unroll
-      for (int c = 0; c < NV; ++c) Uc[c] = oV[c];
-      ldV(g, u.v, i + 1, j, w);
-    } else {
-      lds8(s, SV_, ty, tx, Uc);
-      lds8(s, SV_, ty, txr, w);
-    }
+    for (int c = 0; c < NV; ++c) Uc[c] = oV[c];
+    ldV(g, u.v, i + 1, j, w);
 #pragma unroll
     for (int c = 0; c < NV; ++c) Uc[c] += w[c];
-    if constexpr (F32) {
-      ldV(g, u.v, i, j + 1, q);
-      ldV(g, u.v, i + 1, j + 1, w);
-    } else {
-      lds8(s, SV_, tyu, tx, q);
-      lds8(s, SV_, tyu, txr, w);
-    }
+    ldV(g, u.v, i, j + 1, q);
+    ldV(g, u.v, i + 1, j + 1, w);
 #pragma unroll
     for (int c = 0; c < NV; ++c) Uc[c] = (36.0 * A[c] + f[c] - (Uc[c] + (q[c] + w[c]))) * 0.0625;
     const bool owner = inner && i0 + tx < g.nx && j0 + ty < g.ny;
@@ -567,12 +523,8 @@ __device__ __forceinline__ void points_tile_lean(const Geo& g, CState u, CState 
     }
   }
   auto own_c = [&](double U[NV]) {
-    if constexpr (F32) {
 #pragma unroll
-      for (int c = 0; c < NV; ++c) U[c] = C[c];
-    } else {
-      lds8(s, SC_, ty, tx, U);
-    }
+    for (int c = 0; c < NV; ++c) U[c] = C[c];
   };
   double w[NV], w2[NV];
   pin_acc(PV);
@@ -632,21 +584,8 @@ __device__ __forceinline__ void points_tile_lean(const Geo& g, CState u, CState 
   }
   if (wslot) {
     __syncthreads();  // the LDS is reused as the reduction's scratch
-    block_max_store(wm, ty * PB + tx, PNT, reinterpret_cast<double*>(&s[0][0][0]), wslot);
+    block_max_store(wm, ty * PB + tx, PB * PB, reinterpret_cast<double*>(&s[0][0][0]), wslot);
   }
-}
-
-// One tile of the point update (see above): FP64 stage (R = double) or
-// FP32-bulk stage (R = float).
-// wslot: null, or where the workgroup's maximum of rho_1/dx + rho_2/dy over
-// the values it stores goes (a step's last stage).
-template <class R>
-__device__ __forceinline__ void points_tile(const Geo& g, CState u, CState un, MState out,
-                                            double* __restrict__ src, double dt, double ca, double cb,
-                                            Counters* cn, int bx, int by, R (*s)[PB][PB],
-                                            double* __restrict__ wslot = nullptr) {
-  points_tile_lean<R>(g, u, un, out, src, dt, ca, cb, cn, bx, by, s, wslot, (int)threadIdx.x, (int)threadIdx.y,
-                      true);
 }
 
 // ------------------------------------------------------ fused cell update
