@@ -61,7 +61,8 @@ CUS, CLOCK_HZ = 256, 2.4e9  # MI355X: one wave-instruction issued per CU per cyc
 # The sources the stage kernels k_points / k_cells are built from (the
 # traffic measurement is theirs; the batch and adjoint sources do not enter).
 STAGE_SOURCES = [os.path.join(ROOT, "paper_2506_04857_amd", "csrc", f)
-                 for f in ("af_stage.hip", "af_device.h", "af_points.h", "af_tiles.h")] + [os.path.join(ROOT, "include", "af_mhd.h")]
+                 for f in ("af_stage.hip", "af_cells.h", "af_device.h", "af_points.h", "af_tiles.h")] + [
+                     os.path.join(ROOT, "include", "af_mhd.h")]
 
 
 def source_hash() -> str:

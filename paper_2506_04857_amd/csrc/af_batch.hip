@@ -2,7 +2,7 @@
 // advanced together.  Per SSP-RK3 step: one launch for the dt of every
 // instance (plus its per-instance finish), then per stage either
 //   - one launch (AF_BATCH_FUSED) over the point tiles of all instances
-//     and their cell tiles (512 threads each), which compute their own nine-point sources so that nothing in the
+//     (two per workgroup) and their cell tiles, which compute their own nine-point sources so that nothing in the
 //     launch waits on anything, or
 //   - one launch of the point update over the (instance, tile) work items
 //     of all instances and one launch of the cell update over theirs, with
@@ -29,6 +29,7 @@
 
 #include "af_device.h"
 #include "af_mhd.h"
+#include "af_cells.h"
 #include "af_points.h"
 #include "af_tiles.h"
 
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(point_threads<R>(), point_waves<R>()) void kb_point
 template <class R, int CBX, int CBY, bool PERSIST>
 __global__ __launch_bounds__(CBX * CBY) void kb_cells(const BInst* __restrict__ I, int n, int items, double ca,
                                                       double cb, Counters* cn) {
-  __shared__ CellsLDS<R, CBX, CBY> L;
+  __shared__ CellsTileLDS<R, CBX, CBY> L;
   int it, end, step;
   if (!item_range<PERSIST>(items, it, end, step)) return;
   for (; it < end; it += step) {
@@ -128,22 +129,21 @@ __global__ __launch_bounds__(CBX * CBY) void kb_cells(const BInst* __restrict__ 
     const Geo g = I[m].g;
     const int t = it - I[m].first, ntx = I[m].ntx;
     __syncthreads();
-    cells_tile<R, CBX, CBY>(g, I[m].u, I[m].src, I[m].un.a, I[m].out.a, *I[m].dt, ca, cb, cn, t % ntx,
-                            t / ntx, L);
+    cells_tile_any<R, CBX, CBY>(g, I[m].u, I[m].src, I[m].un.a, I[m].out.a, *I[m].dt, ca, cb, cn, t % ntx, t / ntx, L,
+                                nullptr);
   }
 }
 
 // One stage of every instance in one launch (AF_BATCH_FUSED): workgroups
 // [0, npts) take the point tiles of the batch's point list -- for the FP64
 // stage one each, for the FP32-bulk stage (256 threads a tile) tiles 2q and
-// 2q+1, run side by side by the two halves of the 512-thread workgroup; an odd
-// last tile leaves the second half recomputing the first half's tile without
-// storing anything -- and workgroups [npts, npts + citems) cell tiles.  The
-// two kinds share nothing within the stage: the
-// cell tiles compute their cells' nine-point sources themselves, from the
-// stage input, instead of reading the point tiles' (which would make a cell
-// tile wait for its neighbours' point tiles), so the launch has no
-// inter-workgroup synchronisation at all.
+// 2q+1, run side by side by the two halves of the workgroup; an odd last tile
+// leaves the second half recomputing the first half's tile without storing
+// anything -- and workgroups [npts, npts + citems) cell tiles.  The two kinds
+// share nothing within the stage: the cell tiles compute their cells'
+// nine-point sources themselves, from the stage input, instead of reading the
+// point tiles' (which would make a cell tile wait for its neighbours' point
+// tiles), so the launch has no inter-workgroup synchronisation at all.
 constexpr int FUSED_THREADS = 512;
 template <class R> constexpr int fused_tiles() { return FUSED_THREADS / point_threads<R>(); }
 
@@ -152,37 +152,40 @@ __global__ __launch_bounds__(FUSED_THREADS) void kb_stage(const BInst* __restric
                                                           int n, int pitems, int citems, double ca, double cb,
                                                           Counters* cn) {
   static_assert(CBX * CBY == FUSED_THREADS, "one cell tile per workgroup");
+  constexpr int PER = fused_tiles<R>();
   union Lds {
-    R pts[fused_tiles<R>()][point_fields<R>()][PB][PB];
-    CellsLDS<R, CBX, CBY> cells;
+    R pts[PER][point_fields<R>()][PB][PB];
+    CellsTileLDS<R, CBX, CBY> cells;
   };
   __shared__ Lds L;
-  const int tid = (int)(threadIdx.y * blockDim.x + threadIdx.x);
-  constexpr int PER = fused_tiles<R>();
   const int npts = (pitems + PER - 1) / PER;
   const int it = (int)blockIdx.x;
   if (it < npts) {
-    const int half = PER == 2 ? tid / point_threads<R>() : 0, ltid = PER == 2 ? tid % point_threads<R>() : tid;
-    const int t0 = PER * it + half;
-    const bool live = t0 < pitems;
-    const int t = live ? t0 : PER * it;
-    const int m = find_inst(P, n, t);
-    const Geo g = P[m].g;
-    const int tt = t - P[m].first, ntx = P[m].ntx;
-    if constexpr (PER == 2)
-      points_tile_f32<R>(g, P[m].u, P[m].un, P[m].out, nullptr, *P[m].dt, ca, cb, cn, tt % ntx, tt / ntx,
-                         L.pts[half], nullptr, ltid % PB, ltid / PB, live);
-    else
-      fp64::points_tile(g, P[m].u, P[m].un, P[m].out, P[m].stash, nullptr, *P[m].dt, ca, cb, cn, tt % ntx, tt / ntx,
-                        L.pts[0], nullptr, ltid);
+    if constexpr (PER == 2) {
+      const int half = (int)threadIdx.x / point_threads<R>(), ltid = (int)threadIdx.x % point_threads<R>();
+      const int t0 = 2 * it + half;
+      const bool live = t0 < pitems;
+      const int t = live ? t0 : 2 * it;
+      const int m = find_inst(P, n, t);
+      const Geo g = P[m].g;
+      const int tt = t - P[m].first, ntx = P[m].ntx;
+      points_tile_f32<R>(g, P[m].u, P[m].un, P[m].out, nullptr, *P[m].dt, ca, cb, cn, tt % ntx, tt / ntx, L.pts[half],
+                         nullptr, ltid % PB, ltid / PB, live);
+    } else {
+      const int m = find_inst(P, n, it);
+      const Geo g = P[m].g;
+      const int t = it - P[m].first, ntx = P[m].ntx;
+      points_tile<R>(g, P[m].u, P[m].un, P[m].out, P[m].stash, nullptr, *P[m].dt, ca, cb, cn, t % ntx, t / ntx,
+                     L.pts[0], nullptr);
+    }
     return;
   }
   const int c = it - npts;
   if (c >= citems) return;
   const int m = find_inst(C, n, c);
   const int t = c - C[m].first, ntx = C[m].ntx;
-  cells_tile<R, CBX, CBY>(C[m].g, C[m].u, nullptr, C[m].un.a, C[m].out.a, *C[m].dt, ca, cb, cn, t % ntx, t / ntx,
-                          L.cells);
+  cells_tile_any<R, CBX, CBY>(C[m].g, C[m].u, nullptr, C[m].un.a, C[m].out.a, *C[m].dt, ca, cb, cn, t % ntx, t / ntx,
+                              L.cells, nullptr);
 }
 
 // dt: partial maxima of rho_1/dx + rho_2/dy over DT_CHUNK DoFs per item,
@@ -238,8 +241,8 @@ template <class R, bool P>
 void launch_cells_m(int shape, int grid, hipStream_t s, const BInst* I, int n, int items, double ca, double cb,
                     Counters* cn) {
   const int g = P ? grid : flat_grid(items);
-  if (shape == 0) kb_cells<R, 32, 16, P><<<g, dim3(32, 16), 0, s>>>(I, n, items, ca, cb, cn);
-  else kb_cells<R, 16, 32, P><<<g, dim3(16, 32), 0, s>>>(I, n, items, ca, cb, cn);
+  if (shape == 0) kb_cells<R, 32, 16, P><<<g, 512, 0, s>>>(I, n, items, ca, cb, cn);
+  else kb_cells<R, 16, 32, P><<<g, 512, 0, s>>>(I, n, items, ca, cb, cn);
 }
 template <class R>
 void launch_cells(bool persist, int shape, int grid, hipStream_t s, const BInst* I, int n, int items, double ca,
@@ -258,8 +261,8 @@ template <class R>
 void launch_fused(int shape, hipStream_t s, const BInst* P, const BInst* C, int n, int pitems, int citems,
                   double ca, double cb, Counters* cn) {
   const int grid = (pitems + fused_tiles<R>() - 1) / fused_tiles<R>() + citems;
-  if (shape == 0) kb_stage<R, 32, 16><<<grid, dim3(32, 16), 0, s>>>(P, C, n, pitems, citems, ca, cb, cn);
-  else kb_stage<R, 16, 32><<<grid, dim3(32, 16), 0, s>>>(P, C, n, pitems, citems, ca, cb, cn);
+  if (shape == 0) kb_stage<R, 32, 16><<<grid, FUSED_THREADS, 0, s>>>(P, C, n, pitems, citems, ca, cb, cn);
+  else kb_stage<R, 16, 32><<<grid, FUSED_THREADS, 0, s>>>(P, C, n, pitems, citems, ca, cb, cn);
 }
 template <class R>
 const void* cells_fn(int shape) {

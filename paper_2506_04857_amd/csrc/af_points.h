@@ -71,12 +71,12 @@ __device__ __forceinline__ double jump2(const double a[NV], const double b[NV]) 
 }
 
 // LDS layout (fields of PB x PB values): the states of the tile's V, X, Y (the
-// centre values take V's place once the vertices are finished), then what lines need of each point: 1/rho, total pressure,
-// pressure and c_f in the direction of the lines in flight (both directions
-// for V and the centre).  point_exchange: where the vertical lines' part of
-// the vertex accumulators goes to the other group, on fields that are read no
-// more by then; LIST_: the tile's list of points to limit, on the last of them
-// after that.
+// centre values take V's place once the vertices are finished), then what
+// lines need of each point: 1/rho, total pressure, pressure and c_f in the
+// direction of the lines in flight (both directions for V and the centre).
+// point_exchange: where the vertical lines' part of the vertex accumulators
+// goes to the other group, on fields that are read no more by then; LIST_: the
+// tile's list of points to limit, on the last of them after that.
 constexpr int SV_ = 0, SX_ = 8, SY_ = 16, SC_ = SV_;
 constexpr int QV_ = 24, QX_ = 29, QY_ = 33, QC_ = QV_;  // (1/rho, p_t, p, c_f[, c_f in y])
 constexpr int POINT_FIELDS = 40;

@@ -24,6 +24,7 @@
 #include <string>
 
 #include "af_device.h"
+#include "af_cells.h"
 #include "af_points.h"
 #include "af_tiles.h"
 #include "af_mhd.h"
@@ -65,16 +66,16 @@ __global__ __launch_bounds__(point_threads<R>(), point_waves<R>()) void k_points
 
 template <class R, bool WDT>
 __global__ __launch_bounds__(CBX0 * CBY0) void k_cells(Geo g, CState u, const double* __restrict__ src,
-                                                       const double* __restrict__ un, double* __restrict__ out,
-                                                       const double* dtp, double ca, double cb, Counters* cn,
-                                                       int ntx, int nty, double* __restrict__ wpart) {
-  __shared__ CellsLDS<R, CBX0, CBY0> L;
+                                                       const double* un, double* out, const double* dtp, double ca,
+                                                       double cb, Counters* cn, int ntx, int nty,
+                                                       double* __restrict__ wpart) {
+  __shared__ CellsTileLDS<R, CBX0, CBY0> L;
   int bx, by;
   if (!xcd_tile(ntx, nty, bx, by)) {
-    if (WDT && threadIdx.x == 0 && threadIdx.y == 0) wpart[blockIdx.x] = 0.0;
+    if (WDT && threadIdx.x == 0) wpart[blockIdx.x] = 0.0;
     return;
   }
-  cells_tile<R, CBX0, CBY0>(g, u, src, un, out, *dtp, ca, cb, cn, bx, by, L, WDT ? wpart + blockIdx.x : nullptr);
+  cells_tile_any<R, CBX0, CBY0>(g, u, src, un, out, *dtp, ca, cb, cn, bx, by, L, WDT ? wpart + blockIdx.x : nullptr);
 }
 
 __global__ __launch_bounds__(BLK) void k_dt_partial(Geo g, CState u, double* partial) {
@@ -450,10 +451,10 @@ int run_stage(af_mhd_ctx* c, int k, const af_mhd_state* un, const af_mhd_state* 
   if (e != hipSuccess) return fail(c, AF_EHIP, hipGetErrorString(e));
   const int ctx_ = cells_tiles_x(g), cty = cells_tiles_y(g);
   if (c->f32)
-    (wcells ? k_cells<float, true> : k_cells<float, false>)<<<xcd_grid(ctx_, cty), dim3(CBX0, CBY0), 0, s>>>(
+    (wcells ? k_cells<float, true> : k_cells<float, false>)<<<xcd_grid(ctx_, cty), CBX0 * CBY0, 0, s>>>(
         g, u, c->ws.src, n.a, o.a, dt_dev, A[k], B[k], c->ws.cnt, ctx_, cty, wcells);
   else
-    (wcells ? k_cells<double, true> : k_cells<double, false>)<<<xcd_grid(ctx_, cty), dim3(CBX0, CBY0), 0, s>>>(
+    (wcells ? k_cells<double, true> : k_cells<double, false>)<<<xcd_grid(ctx_, cty), CBX0 * CBY0, 0, s>>>(
         g, u, c->ws.src, n.a, o.a, dt_dev, A[k], B[k], c->ws.cnt, ctx_, cty, wcells);
   e = timer_end(c, end);
   if (e != hipSuccess) return fail(c, AF_EHIP, hipGetErrorString(e));

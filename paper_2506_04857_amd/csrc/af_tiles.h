@@ -1,9 +1,9 @@
 // af_tiles.h -- the tile bodies of one SSP-RK3 stage of the PP Active Flux
 // scheme for 2D ideal MHD with the Godunov-Powell source (gfx950): the
-// FP32-bulk point update (points_tile; the FP64 one is in af_points.h) and
-// the cell update (cells_tile), the XCD-aware tile order and the reduction
-// helpers.  Shared by the single-grid kernels (af_stage.hip) and the batched
-// kernels (af_batch.hip).
+// FP32-bulk stage's point and cell update (the FP64 stage's are in af_points.h
+// and af_cells.h), the XCD-aware tile order and the reduction helpers.  Shared
+// by the single-grid kernels (af_stage.hip) and the batched kernels
+// (af_batch.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -588,7 +588,7 @@ __device__ __forceinline__ void points_tile_f32(const Geo& g, CState u, CState u
   }
 }
 
-// ------------------------------------------------------ fused cell update
+// ---------------------------------- fused cell update of the FP32-bulk stage
 // One launch computes the cell averages of the stage for a tile of
 // (CBX-3) x (CBY-3) cells; the block's CBX x CBY threads cover the cells
 // whose flux-limiter box is needed plus one trailing row/column whose left
@@ -740,16 +740,15 @@ __device__ __forceinline__ R sensor_theta(R kappa, const R a[4], const R b[4], i
   return exp_r(-kappa * (p1 * p2 + p3));
 }
 
-// LDS of one cell tile.  The Lambda exchange is FP64: for the FP64 stage it
-// reuses the exchange buffer, for the FP32-bulk stage it has its own.
+// LDS of one cell tile.
 template <class R, int CBX, int CBY>
 struct CellsLDS {
   R dfx[NV][CBY][CBX];  // theta^s (F_simpson - F^LLF) at the x-interface left of each cell
   R dfy[NV][CBY][CBX];  // ... at the y-interface below it; they give H_L, H_R, H_D, H_U
-  R x[RF][CBY][CBX];    // exchange: primitives; records (0-3) and F^LLF (4-11); Lambda (FP64 stage)
+  R x[RF][CBY][CBX];    // exchange: primitives; records (0-3) and F^LLF (4-11)
   R ts[2][CBY][CBX];    // theta^s at the two interfaces
   R phi[4][CBY + 1][CBX + 1];  // indicator-major: a wavefront's lanes read consecutive words
-  double lam[IsF32<R>::value ? 4 : 1][CBY][CBX];
+  double lam[4][CBY][CBX];     // Lambda
 };
 
 // One tile of the cell update: CBX x CBY threads, (CBX-3) x (CBY-3) cells.
@@ -766,12 +765,7 @@ __device__ __forceinline__ void cells_tile(const Geo& g, CState u, const double*
   auto& s_x = L.x;
   auto& s_ts = L.ts;
   auto& s_phi = L.phi;
-  double (*s_lam)[CBY][CBX];
-  if constexpr (IsF32<R>::value) {
-    s_lam = L.lam;
-  } else {
-    s_lam = reinterpret_cast<double (*)[CBY][CBX]>(&L.x[0][0][0]);
-  }
+  auto& s_lam = L.lam;
   // thread (tx, ty) of the CBX x CBY tile: x fastest in the flat thread index
   const int tid = (int)(threadIdx.y * blockDim.x + threadIdx.x), tx = tid % CBX, ty = tid / CBX;
   const int i0 = bx * (CBX - 3) - 1, j0 = by * (CBY - 3) - 1;
@@ -804,16 +798,6 @@ __device__ __forceinline__ void cells_tile(const Geo& g, CState u, const double*
     }
   }
   __syncthreads();
-  // div B of the LLF source (phase 4) from the neighbours' B1, B2: for the
-  // FP64 stage from the sensor primitives (they hold B exactly), read before
-  // the next barrier, after which the exchange buffer they share is
-  // rewritten; for the FP32-bulk stage from memory in phase 4
-  double divb = 0.0;
-  if constexpr (!IsF32<R>::value) {
-    const int pc = (ty + 2) * PW + (tx + 2);
-    divb = (prim[3 * PW * PH + pc + 1] - prim[3 * PW * PH + pc - 1]) * (0.5 * g.rdx);
-    divb += (prim[4 * PW * PH + pc + PW] - prim[4 * PW * PH + pc - PW]) * (0.5 * g.rdy);
-  }
   // the cell's average, nine-point source and first edge point: loaded
   // now, in flight while the indicators are computed
   double A[NV], Sd[NV], w0[NV];
@@ -953,17 +937,15 @@ __device__ __forceinline__ void cells_tile(const Geo& g, CState u, const double*
   R Sl[NV];
   {
     R P[NV];
-    if constexpr (IsF32<R>::value) {
-      double AN[NV], b;
-      ldA(g, u.a, i + 1, j, AN);
-      b = AN[4];
-      ldA(g, u.a, i - 1, j, AN);
-      divb = (b - AN[4]) * (0.5 * g.rdx);
-      ldA(g, u.a, i, j + 1, AN);
-      b = AN[5];
-      ldA(g, u.a, i, j - 1, AN);
-      divb += (b - AN[5]) * (0.5 * g.rdy);
-    }
+    double AN[NV], b, divb;
+    ldA(g, u.a, i + 1, j, AN);
+    b = AN[4];
+    ldA(g, u.a, i - 1, j, AN);
+    divb = (b - AN[4]) * (0.5 * g.rdx);
+    ldA(g, u.a, i, j + 1, AN);
+    b = AN[5];
+    ldA(g, u.a, i, j - 1, AN);
+    divb += (b - AN[5]) * (0.5 * g.rdy);
     psi(A, P);
 #pragma unroll
     for (int c = 0; c < NV; ++c) {
