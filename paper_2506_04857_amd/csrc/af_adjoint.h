@@ -55,25 +55,60 @@ constexpr double LAMBDA_REG = 1e-12;  // regulariser of the density box
 constexpr double SHRINK = 1e-8;       // round-off fallback step 2^m * 1e-8
 constexpr double SENSOR_TINY = 1e-40;
 
+// Division and square root.  On the host they are the plain ones.  On the GPU
+// a / By(b) multiplies by b's reciprocal (hardware approximation, two Newton
+// steps: formed once for all the quotients by b that a kernel takes) and
+// corrects the quotient by its residual, and root() is the hardware's
+// reciprocal root, one Newton step and a correction of the root itself.  Both
+// round like the IEEE operations but for rare last-place differences
+// (subnormal and infinite arguments aside, which admissible states do not
+// have); an exact cancellation stays exact, equal quotients being formed by
+// equal operations.  The compiler's own sequences scale and fix up every
+// quotient: 10 to 14 dependent instructions each where this takes 3 and shares
+// the rest.  A stage's recording and reverse kernels hold 30 to 200 quotients
+// an entity and run on one or two waves per SIMD, so that this chain was most
+// of their time.
+struct By {
+  double b;
+  AF_HD explicit By(double x) : b(x) {}
+};
+AF_HD double operator/(double a, By d) {
+#ifdef __HIP_DEVICE_COMPILE__
+  double r = __builtin_amdgcn_rcp(d.b);
+  r = fma(r, fma(-d.b, r, 1.0), r);
+  r = fma(r, fma(-d.b, r, 1.0), r);
+  const double q = a * r;
+  return fma(fma(-d.b, q, a), r, q);
+#else
+  return a / d.b;
+#endif
+}
+AF_HD double root(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  double r = __builtin_amdgcn_rsq(x);
+  r = r * fma(-(0.5 * x) * r, r, 1.5);
+  double q = x * r;
+  q = fma(fma(-q, q, x), 0.5 * r, q);
+  return x == 0.0 ? 0.0 : q;
+#else
+  return sqrt(x);
+#endif
+}
+
 struct AGeo {
   int nx, ny, nxp, nyp, bcx, bcy;
   double dx, dy, gamma, kappa;
 };
 
+// Stencils reach at most n beyond either end.
 AF_HD int mcell(int i, int n, int bc) {
-  if (bc == 0) {
-    i %= n;
-    return i < 0 ? i + n : i;
-  }
+  if (bc == 0) return i < 0 ? i + n : i >= n ? i - n : i;
   if (i < 0) return -1 - i;
   if (i >= n) return 2 * n - 1 - i;
   return i;
 }
 AF_HD int mnode(int k, int n, int bc) {
-  if (bc == 0) {
-    k %= n;
-    return k < 0 ? k + n : k;
-  }
+  if (bc == 0) return k < 0 ? k + n : k >= n ? k - n : k;
   if (k < 0) return -k;
   if (k > n) return 2 * n - k;
   return k;
@@ -115,13 +150,13 @@ AF_HD double dmin(double a, double b) { return b < a ? b : a; }  // ties: first
 AF_HD double pres(const double* U, double g) {
   const double m2 = U[1] * U[1] + U[2] * U[2] + U[3] * U[3];
   const double b2 = U[4] * U[4] + U[5] * U[5] + U[6] * U[6];
-  return (g - 1.0) * (U[7] - m2 / (2.0 * U[0]) - b2 / 2.0);
+  return (g - 1.0) * (U[7] - 0.5 * m2 / By(U[0]) - b2 / 2.0);
 }
 AF_HD bool admissible(const double* U, double g) { return U[0] > 0.0 && pres(U, g) > 0.0; }
 // lU += lp dp/dU
 AF_HD void pres_vjp(const double* U, double g, double lp, double* lU) {
   const double r = U[0];
-  const double v1 = U[1] / r, v2 = U[2] / r, v3 = U[3] / r;
+  const double v1 = U[1] / By(r), v2 = U[2] / By(r), v3 = U[3] / By(r);
   const double gm = (g - 1.0) * lp;
   lU[0] += gm * 0.5 * (v1 * v1 + v2 * v2 + v3 * v3);
   lU[1] -= gm * v1;
@@ -136,7 +171,7 @@ AF_HD void pres_vjp(const double* U, double g, double lp, double* lU) {
 // Physical flux F_n (n = 0: x, 1: y), Section 1.
 AF_HD void flux(const double* U, double g, int n, double* F) {
   const double rho = U[0];
-  const double v[3] = {U[1] / rho, U[2] / rho, U[3] / rho};
+  const double v[3] = {U[1] / By(rho), U[2] / By(rho), U[3] / By(rho)};
   const double B[3] = {U[4], U[5], U[6]};
   const double p = pres(U, g);
   const double pt = p + (B[0] * B[0] + B[1] * B[1] + B[2] * B[2]) / 2.0;
@@ -149,7 +184,7 @@ AF_HD void flux(const double* U, double g, int n, double* F) {
 // lU += (dF_n/dU)^T lF
 AF_HD void flux_vjp(const double* U, double g, int n, const double* lF, double* lU) {
   const double rho = U[0];
-  const double v[3] = {U[1] / rho, U[2] / rho, U[3] / rho};
+  const double v[3] = {U[1] / By(rho), U[2] / By(rho), U[3] / By(rho)};
   const double B[3] = {U[4], U[5], U[6]};
   const double E = U[7];
   const double p = pres(U, g);
@@ -198,8 +233,8 @@ AF_HD void flux_vjp(const double* U, double g, int n, const double* lF, double* 
   }
   // v = m / rho
   for (int i = 0; i < 3; ++i) {
-    lU[1 + i] += lv[i] / rho;
-    lr -= lv[i] * v[i] / rho;
+    lU[1 + i] += lv[i] / By(rho);
+    lr -= lv[i] * v[i] / By(rho);
     lU[4 + i] += lB[i];
   }
   lU[0] += lr;
@@ -209,60 +244,60 @@ AF_HD void flux_vjp(const double* U, double g, int n, const double* lF, double* 
 // Fast magnetosonic speed c_{f,n}, with the inner discriminant clamped at 0.
 AF_HD double cfast(const double* U, double g, int n) {
   const double rho = U[0];
-  const double c2 = g * pres(U, g) / rho;
-  const double b2 = (U[4] * U[4] + U[5] * U[5] + U[6] * U[6]) / rho;
+  const double c2 = g * pres(U, g) / By(rho);
+  const double b2 = (U[4] * U[4] + U[5] * U[5] + U[6] * U[6]) / By(rho);
   const double Bl = U[4 + n];
   const double s = c2 + b2;
-  double disc = s * s - 4.0 * c2 * Bl * Bl / rho;
+  double disc = s * s - 4.0 * c2 * Bl * Bl / By(rho);
   if (disc < 0.0) disc = 0.0;
-  return sqrt(0.5 * (s + sqrt(disc)));
+  return root(0.5 * (s + root(disc)));
 }
 AF_HD void cfast_vjp(const double* U, double g, int n, double lc, double* lU) {
   const double rho = U[0];
   const double p = pres(U, g);
-  const double c2 = g * p / rho;
+  const double c2 = g * p / By(rho);
   const double bb = U[4] * U[4] + U[5] * U[5] + U[6] * U[6];
-  const double b2 = bb / rho;
+  const double b2 = bb / By(rho);
   const double Bl = U[4 + n];
   const double s = c2 + b2;
-  double disc = s * s - 4.0 * c2 * Bl * Bl / rho;
+  double disc = s * s - 4.0 * c2 * Bl * Bl / By(rho);
   const bool clamped = disc < 0.0;
   if (clamped) disc = 0.0;
-  const double rd = sqrt(disc);
-  const double cf = sqrt(0.5 * (s + rd));
+  const double rd = root(disc);
+  const double cf = root(0.5 * (s + rd));
   if (!(cf > 0.0)) return;
-  const double lcf2 = lc / (2.0 * cf);
+  const double lcf2 = lc / By(2.0 * cf);
   double ls = 0.5 * lcf2;
   const double lrd = 0.5 * lcf2;
-  const double ldisc = (!clamped && rd > 0.0) ? lrd / (2.0 * rd) : 0.0;
+  const double ldisc = (!clamped && rd > 0.0) ? lrd / By(2.0 * rd) : 0.0;
   ls += ldisc * 2.0 * s;
-  double lc2 = -ldisc * 4.0 * Bl * Bl / rho;
-  const double lBl = -ldisc * 8.0 * c2 * Bl / rho;
-  double lr = ldisc * 4.0 * c2 * Bl * Bl / (rho * rho);
+  double lc2 = -ldisc * 4.0 * Bl * Bl / By(rho);
+  const double lBl = -ldisc * 8.0 * c2 * Bl / By(rho);
+  double lr = ldisc * 4.0 * c2 * Bl * Bl / By(rho * rho);
   lc2 += ls;
   const double lb2 = ls;
-  for (int i = 0; i < 3; ++i) lU[4 + i] += lb2 * 2.0 * U[4 + i] / rho;
-  lr -= lb2 * bb / (rho * rho);
-  const double lp = lc2 * g / rho;
-  lr -= lc2 * g * p / (rho * rho);
+  for (int i = 0; i < 3; ++i) lU[4 + i] += lb2 * 2.0 * U[4 + i] / By(rho);
+  lr -= lb2 * bb / By(rho * rho);
+  const double lp = lc2 * g / By(rho);
+  lr -= lc2 * g * p / By(rho * rho);
   lU[4 + n] += lBl;
   lU[0] += lr;
   pres_vjp(U, g, lp, lU);
 }
 
 // Spectral radius |v_n| + c_{f,n} (Section 2.3).
-AF_HD double srad(const double* U, double g, int n) { return fabs(U[1 + n] / U[0]) + cfast(U, g, n); }
+AF_HD double srad(const double* U, double g, int n) { return fabs(U[1 + n] / By(U[0])) + cfast(U, g, n); }
 AF_HD void srad_vjp(const double* U, double g, int n, double l, double* lU) {
-  const double v = U[1 + n] / U[0];
+  const double v = U[1 + n] / By(U[0]);
   const double lv = l * sgn(v);
-  lU[1 + n] += lv / U[0];
-  lU[0] -= lv * v / U[0];
+  lU[1 + n] += lv / By(U[0]);
+  lU[0] -= lv * v / By(U[0]);
   cfast_vjp(U, g, n, l, lU);
 }
 
 // Godunov-Powell source vector Psi = (0, B, v, v.B).
 AF_HD void psi(const double* U, double* P) {
-  const double v1 = U[1] / U[0], v2 = U[2] / U[0], v3 = U[3] / U[0];
+  const double v1 = U[1] / By(U[0]), v2 = U[2] / By(U[0]), v3 = U[3] / By(U[0]);
   P[0] = 0.0;
   P[1] = U[4];
   P[2] = U[5];
@@ -275,31 +310,31 @@ AF_HD void psi(const double* U, double* P) {
 AF_HD void psi_vjp(const double* U, const double* lP, double* lU) {
   const double rho = U[0];
   for (int i = 0; i < 3; ++i) {
-    const double v = U[1 + i] / rho;
+    const double v = U[1 + i] / By(rho);
     const double lv = lP[4 + i] + lP[7] * U[4 + i];
     lU[4 + i] += lP[1 + i] + lP[7] * v;
-    lU[1 + i] += lv / rho;
-    lU[0] -= lv * v / rho;
+    lU[1 + i] += lv / By(rho);
+    lU[0] -= lv * v / By(rho);
   }
 }
 
 // alpha_{n,*}(a, b) of the Lemma of Section 3.1.
 AF_HD double astar(const double* a, const double* b, double g, int n) {
-  const double sa = sqrt(a[0]), sb = sqrt(b[0]);
-  const double va = a[1 + n] / a[0], vb = b[1 + n] / b[0];
-  const double t1 = dmax(fabs(va), fabs(sa * va + sb * vb) / (sa + sb));
+  const double sa = root(a[0]), sb = root(b[0]);
+  const double va = a[1 + n] / By(a[0]), vb = b[1 + n] / By(b[0]);
+  const double t1 = dmax(fabs(va), fabs(sa * va + sb * vb) / By(sa + sb));
   const double t2 = dmax(cfast(a, g, n), cfast(b, g, n));
   const double d1 = a[4] - b[4], d2 = a[5] - b[5], d3 = a[6] - b[6];
-  const double t3 = sqrt(d1 * d1 + d2 * d2 + d3 * d3) / (sa + sb);
+  const double t3 = root(d1 * d1 + d2 * d2 + d3 * d3) / By(sa + sb);
   return t1 + t2 + t3;
 }
 AF_HD void astar_vjp(const double* a, const double* b, double g, int n, double l, double* la, double* lb) {
-  const double sa = sqrt(a[0]), sb = sqrt(b[0]);
-  const double va = a[1 + n] / a[0], vb = b[1 + n] / b[0];
+  const double sa = root(a[0]), sb = root(b[0]);
+  const double va = a[1 + n] / By(a[0]), vb = b[1 + n] / By(b[0]);
   const double den = sa + sb, num = sa * va + sb * vb;
   double lsa = 0.0, lsb = 0.0, lva = 0.0, lvb = 0.0;
-  if (fabs(va) < fabs(num) / den) {
-    const double lnum = l * sgn(num) / den, lden = -l * fabs(num) / (den * den);
+  if (fabs(va) < fabs(num) / By(den)) {
+    const double lnum = l * sgn(num) / By(den), lden = -l * fabs(num) / By(den * den);
     lsa += lnum * va + lden;
     lsb += lnum * vb + lden;
     lva += lnum * sa;
@@ -312,22 +347,22 @@ AF_HD void astar_vjp(const double* a, const double* b, double g, int n, double l
   else
     cfast_vjp(a, g, n, l, la);
   const double d[3] = {a[4] - b[4], a[5] - b[5], a[6] - b[6]};
-  const double nrm = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-  const double lden3 = -l * nrm / (den * den);
+  const double nrm = root(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+  const double lden3 = -l * nrm / By(den * den);
   lsa += lden3;
   lsb += lden3;
   if (nrm > 0.0)
     for (int i = 0; i < 3; ++i) {
-      const double t = l / den * d[i] / nrm;
+      const double t = l / By(den) * d[i] / By(nrm);
       la[4 + i] += t;
       lb[4 + i] -= t;
     }
-  la[0] += lsa / (2.0 * sa);
-  lb[0] += lsb / (2.0 * sb);
-  la[1 + n] += lva / a[0];
-  la[0] -= lva * va / a[0];
-  lb[1 + n] += lvb / b[0];
-  lb[0] -= lvb * vb / b[0];
+  la[0] += lsa / By(2.0 * sa);
+  lb[0] += lsb / By(2.0 * sb);
+  la[1 + n] += lva / By(a[0]);
+  la[0] -= lva * va / By(a[0]);
+  lb[1 + n] += lvb / By(b[0]);
+  lb[0] -= lvb * vb / By(b[0]);
 }
 
 // LLF viscosity: the Lemma's bound with equality,
@@ -397,13 +432,13 @@ AF_HD void fvs_line(const double* const w[5], double g, int n, double h, double*
       Fp[m] = 0.5 * (F[m][c] + alpha * w[m][c]);
       Fm[m] = 0.5 * (F[m][c] - alpha * w[m][c]);
     }
-    const double Dp = (Fp[0] - 4.0 * Fp[1] + 3.0 * Fp[2]) / h;
-    const double Dm = (-3.0 * Fm[2] + 4.0 * Fm[3] - Fm[4]) / h;
+    const double Dp = (Fp[0] - 4.0 * Fp[1] + 3.0 * Fp[2]) / By(h);
+    const double Dm = (-3.0 * Fm[2] + 4.0 * Fm[3] - Fm[4]) / By(h);
     R[c] = Dp + Dm;
   }
   const int b = 4 + n;
-  const double Bp = (w[0][b] - 4.0 * w[1][b] + 3.0 * w[2][b]) / h;
-  const double Bm = (-3.0 * w[2][b] + 4.0 * w[3][b] - w[4][b]) / h;
+  const double Bp = (w[0][b] - 4.0 * w[1][b] + 3.0 * w[2][b]) / By(h);
+  const double Bm = (-3.0 * w[2][b] + 4.0 * w[3][b] - w[4][b]) / By(h);
   dB = 0.5 * (Bp + Bm);
 }
 AF_HD void fvs_line_vjp(const double* const w[5], double g, int n, double h, const double* lR, double ldB,
@@ -421,7 +456,7 @@ AF_HD void fvs_line_vjp(const double* const w[5], double g, int n, double h, con
   }
   double lal = 0.0;
   for (int m = 0; m < 5; ++m) {
-    const double sp = 0.5 * (cp[m] + cm[m]) / h, sd = 0.5 * (cp[m] - cm[m]) / h;
+    const double sp = 0.5 * (cp[m] + cm[m]) / By(h), sd = 0.5 * (cp[m] - cm[m]) / By(h);
     double lF[NV];
     for (int c = 0; c < NV; ++c) {
       lF[c] = sp * lR[c];
@@ -443,22 +478,22 @@ AF_HD void point_llf(const double* U, const double* L, const double* R, const do
   llf(L, U, g.gamma, 0, FL);
   llf(U, Up, g.gamma, 1, FU);
   llf(D, U, g.gamma, 1, FD);
-  const double divB = (R[4] - L[4]) / (2.0 * g.dx) + (Up[5] - D[5]) / (2.0 * g.dy);
+  const double divB = (R[4] - L[4]) / By(2.0 * g.dx) + (Up[5] - D[5]) / By(2.0 * g.dy);
   psi(U, P);
   for (int c = 0; c < NV; ++c)
-    W[c] = U[c] - dt / g.dx * (FR[c] - FL[c]) - dt / g.dy * (FU[c] - FD[c]) - dt * divB * P[c];
+    W[c] = U[c] - dt / By(g.dx) * (FR[c] - FL[c]) - dt / By(g.dy) * (FU[c] - FD[c]) - dt * divB * P[c];
 }
 AF_HD void point_llf_vjp(const double* U, const double* L, const double* R, const double* D, const double* Up,
                          double dt, const AGeo& g, const double* lW, double* lU, double* lL, double* lR, double* lD,
                          double* lUp) {
   double P[NV], lx[NV], ly[NV], lP[NV];
   psi(U, P);
-  const double divB = (R[4] - L[4]) / (2.0 * g.dx) + (Up[5] - D[5]) / (2.0 * g.dy);
+  const double divB = (R[4] - L[4]) / By(2.0 * g.dx) + (Up[5] - D[5]) / By(2.0 * g.dy);
   double ldiv = 0.0;
   for (int c = 0; c < NV; ++c) {
     lU[c] += lW[c];
-    lx[c] = -dt / g.dx * lW[c];
-    ly[c] = -dt / g.dy * lW[c];
+    lx[c] = -dt / By(g.dx) * lW[c];
+    ly[c] = -dt / By(g.dy) * lW[c];
     ldiv -= dt * lW[c] * P[c];
     lP[c] = -dt * divB * lW[c];
   }
@@ -469,10 +504,10 @@ AF_HD void point_llf_vjp(const double* U, const double* L, const double* R, cons
   for (int c = 0; c < NV; ++c) ly[c] = -ly[c];
   llf_vjp(D, U, g.gamma, 1, ly, lD, lU);
   psi_vjp(U, lP, lU);
-  lR[4] += ldiv / (2.0 * g.dx);
-  lL[4] -= ldiv / (2.0 * g.dx);
-  lUp[5] += ldiv / (2.0 * g.dy);
-  lD[5] -= ldiv / (2.0 * g.dy);
+  lR[4] += ldiv / By(2.0 * g.dx);
+  lL[4] -= ldiv / By(2.0 * g.dx);
+  lUp[5] += ldiv / By(2.0 * g.dy);
+  lD[5] -= ldiv / By(2.0 * g.dy);
 }
 
 // ------------------------------------------------- scaling limiters
@@ -526,7 +561,7 @@ AF_HD void point_limit(const double* UH, const double* UL, double g, double* out
   }
   double th1 = 1.0;
   if (UH[0] < er) {
-    th1 = (rhoL - er) / (rhoL - UH[0]);
+    th1 = (rhoL - er) / By(rhoL - UH[0]);
     fl |= BL_T1;
   }
   double Us[NV];
@@ -535,7 +570,7 @@ AF_HD void point_limit(const double* UH, const double* UL, double g, double* out
   const double ps = pres(Us, g);
   double th2 = 1.0;
   if (ps < ep) {
-    th2 = (pL - ep) / (pL - ps);
+    th2 = (pL - ep) / By(pL - ps);
     fl |= BL_T2;
   }
   th2 = fallback(th2, Us, UL, g, fl);
@@ -545,12 +580,12 @@ AF_HD void point_limit_vjp(const double* UH, const double* UL, double g, uint32_
                            double* lUH, double* lUL) {
   const double rhoL = UL[0], pL = pres(UL, g);
   const double er = (fl & BL_ER) ? rhoL : EPS_FLOOR, ep = (fl & BL_EP) ? pL : EPS_FLOOR;
-  const double th1 = (fl & BL_T1) ? (rhoL - er) / (rhoL - UH[0]) : 1.0;
+  const double th1 = (fl & BL_T1) ? (rhoL - er) / By(rhoL - UH[0]) : 1.0;
   double Us[NV];
   for (int c = 0; c < NV; ++c) Us[c] = UH[c];
   Us[0] = th1 * UH[0] + (1.0 - th1) * rhoL;
   const double ps = pres(Us, g);
-  const double th2r = (fl & BL_T2) ? (pL - ep) / (pL - ps) : 1.0;
+  const double th2r = (fl & BL_T2) ? (pL - ep) / By(pL - ps) : 1.0;
   const double th2 = fallback_apply(th2r, fl);
   double lUs[NV], lth2 = 0.0;
   for (int c = 0; c < NV; ++c) {
@@ -562,7 +597,7 @@ AF_HD void point_limit_vjp(const double* UH, const double* UL, double g, uint32_
   double lpL = 0.0, lep = 0.0, lrhoL = 0.0, ler = 0.0;
   if (fl & BL_T2) {
     const double den = pL - ps;
-    const double ln = lth2 / den, ldn = -lth2 * th2r / den;
+    const double ln = lth2 / By(den), ldn = -lth2 * th2r / By(den);
     lpL += ln + ldn;
     lep -= ln;
     pres_vjp(Us, g, -ldn, lUs);
@@ -573,7 +608,7 @@ AF_HD void point_limit_vjp(const double* UH, const double* UL, double g, uint32_
   const double lth1 = lUs[0] * (UH[0] - rhoL);
   if (fl & BL_T1) {
     const double den = rhoL - UH[0];
-    const double ln = lth1 / den, ldn = -lth1 * th1 / den;
+    const double ln = lth1 / By(den), ldn = -lth1 * th1 / By(den);
     lrhoL += ln + ldn;
     ler -= ln;
     lUH[0] -= ldn;
@@ -607,7 +642,7 @@ AF_HD void centre_limit(const double* A, const double* Uc, double g, double* C, 
   }
   double th1 = 1.0;
   if (Uc[0] < er) {
-    th1 = (rhoA - er) / (rhoA - Uc[0]);
+    th1 = (rhoA - er) / By(rhoA - Uc[0]);
     fl |= BL_T1;
   }
   double Ur[NV];
@@ -615,7 +650,7 @@ AF_HD void centre_limit(const double* A, const double* Uc, double g, double* C, 
   const double pr = pres(Ur, g);
   double th2 = 1.0;
   if (pr < ep) {
-    th2 = (pA - ep) / (pA - pr);
+    th2 = (pA - ep) / By(pA - pr);
     fl |= BL_T2;
   }
   th2 = fallback(th2, Ur, A, g, fl);
@@ -626,11 +661,11 @@ AF_HD void centre_limit_vjp(const double* A, const double* Uc, double g, uint32_
                             double* lUc) {
   const double rhoA = A[0], pA = pres(A, g);
   const double er = (fl & BL_ER) ? rhoA : EPS_FLOOR, ep = (fl & BL_EP) ? pA : EPS_FLOOR;
-  const double th1 = (fl & BL_T1) ? (rhoA - er) / (rhoA - Uc[0]) : 1.0;
+  const double th1 = (fl & BL_T1) ? (rhoA - er) / By(rhoA - Uc[0]) : 1.0;
   double Ur[NV];
   for (int c = 0; c < NV; ++c) Ur[c] = th1 * Uc[c] + (1.0 - th1) * A[c];
   const double pr = pres(Ur, g);
-  const double th2r = (fl & BL_T2) ? (pA - ep) / (pA - pr) : 1.0;
+  const double th2r = (fl & BL_T2) ? (pA - ep) / By(pA - pr) : 1.0;
   const double th2 = fallback_apply(th2r, fl);
   double lUr[NV], lth2 = 0.0;
   for (int c = 0; c < NV; ++c) {
@@ -642,7 +677,7 @@ AF_HD void centre_limit_vjp(const double* A, const double* Uc, double g, uint32_
   double lpA = 0.0, lep = 0.0, lrhoA = 0.0, ler = 0.0;
   if (fl & BL_T2) {
     const double den = pA - pr;
-    const double ln = lth2 / den, ldn = -lth2 * th2r / den;
+    const double ln = lth2 / By(den), ldn = -lth2 * th2r / By(den);
     lpA += ln + ldn;
     lep -= ln;
     pres_vjp(Ur, g, -ldn, lUr);
@@ -655,7 +690,7 @@ AF_HD void centre_limit_vjp(const double* A, const double* Uc, double g, uint32_
   }
   if (fl & BL_T1) {
     const double den = rhoA - Uc[0];
-    const double ln = lth1 / den, ldn = -lth1 * th1 / den;
+    const double ln = lth1 / By(den), ldn = -lth1 * th1 / By(den);
     lrhoA += ln + ldn;
     ler -= ln;
     lUc[0] -= ldn;
@@ -683,8 +718,8 @@ AF_HD void cell_source(const double* const P[3][3], const AGeo& g, double* S) {
   zero8(S);
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) {
-      const double dB1 = d3(a, P[0][b][4], P[1][b][4], P[2][b][4]) / g.dx;
-      const double dB2 = d3(b, P[a][0][5], P[a][1][5], P[a][2][5]) / g.dy;
+      const double dB1 = d3(a, P[0][b][4], P[1][b][4], P[2][b][4]) / By(g.dx);
+      const double dB2 = d3(b, P[a][0][5], P[a][1][5], P[a][2][5]) / By(g.dy);
       const double divB = dB1 + dB2;
       double Q[NV];
       psi(P[a][b], Q);
@@ -695,8 +730,8 @@ AF_HD void cell_source_vjp(const double* const P[3][3], const AGeo& g, const dou
   const double w[3] = {1.0 / 6.0, 2.0 / 3.0, 1.0 / 6.0};
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) {
-      const double dB1 = d3(a, P[0][b][4], P[1][b][4], P[2][b][4]) / g.dx;
-      const double dB2 = d3(b, P[a][0][5], P[a][1][5], P[a][2][5]) / g.dy;
+      const double dB1 = d3(a, P[0][b][4], P[1][b][4], P[2][b][4]) / By(g.dx);
+      const double dB2 = d3(b, P[a][0][5], P[a][1][5], P[a][2][5]) / By(g.dy);
       const double divB = dB1 + dB2;
       double Q[NV], lQ[NV], ldiv = 0.0;
       psi(P[a][b], Q);
@@ -706,8 +741,8 @@ AF_HD void cell_source_vjp(const double* const P[3][3], const AGeo& g, const dou
       }
       psi_vjp(P[a][b], lQ, lP[a][b]);
       for (int q = 0; q < 3; ++q) {
-        lP[q][b][4] += d3c(a, q) * ldiv / g.dx;
-        lP[a][q][5] += d3c(b, q) * ldiv / g.dy;
+        lP[q][b][4] += d3c(a, q) * ldiv / By(g.dx);
+        lP[a][q][5] += d3c(b, q) * ldiv / By(g.dy);
       }
     }
 }
@@ -736,14 +771,14 @@ AF_HD void sensor(const double* c, const double* l, const double* r, const doubl
                ptu = ptot(u, g.gamma);
   const double n1x = ptr - 2.0 * ptc + ptl, d1x = ptr + 2.0 * ptc + ptl;
   const double n1y = ptu - 2.0 * ptc + ptd, d1y = ptu + 2.0 * ptc + ptd;
-  phi[0] = fabs(n1x) / fabs(d1x);
-  phi[1] = fabs(n1y) / fabs(d1y);
-  const double divv = (r[1] / r[0] - l[1] / l[0]) / (2.0 * g.dx) + (u[2] / u[0] - d[2] / d[0]) / (2.0 * g.dy);
-  const double curlv = (r[2] / r[0] - l[2] / l[0]) / (2.0 * g.dx) - (u[1] / u[0] - d[1] / d[0]) / (2.0 * g.dy);
-  const double q = -divv / sqrt(divv * divv + curlv * curlv + SENSOR_TINY);
+  phi[0] = fabs(n1x) / By(fabs(d1x));
+  phi[1] = fabs(n1y) / By(fabs(d1y));
+  const double divv = (r[1] / By(r[0]) - l[1] / By(l[0])) / By(2.0 * g.dx) + (u[2] / By(u[0]) - d[2] / By(d[0])) / By(2.0 * g.dy);
+  const double curlv = (r[2] / By(r[0]) - l[2] / By(l[0])) / By(2.0 * g.dx) - (u[1] / By(u[0]) - d[1] / By(d[0])) / By(2.0 * g.dy);
+  const double q = -divv / By(root(divv * divv + curlv * curlv + SENSOR_TINY));
   phi[2] = q < 0.0 ? 0.0 : q;
   const double n3 = r[4] - l[4] + u[5] - d[5], s3 = c[4] + c[5];
-  phi[3] = fabs(n3) / (fabs(s3) + SENSOR_TINY);
+  phi[3] = fabs(n3) / By(fabs(s3) + SENSOR_TINY);
   fl = (q < 0.0 ? 0u : (uint32_t)SN_PHI2) | (n1x < 0.0 ? (uint32_t)SN_N1X : 0u) | (d1x < 0.0 ? (uint32_t)SN_D1X : 0u) |
        (n1y < 0.0 ? (uint32_t)SN_N1Y : 0u) | (d1y < 0.0 ? (uint32_t)SN_D1Y : 0u) | (n3 < 0.0 ? (uint32_t)SN_N3 : 0u) |
        (s3 < 0.0 ? (uint32_t)SN_D3 : 0u);
@@ -757,7 +792,7 @@ AF_HD void sensor_vjp(const double* c, const double* l, const double* r, const d
   {  // phi1x = |N| / |D|
     const double N = ptr - 2.0 * ptc + ptl, D = ptr + 2.0 * ptc + ptl;
     const double sN = (fl & SN_N1X) ? -1.0 : 1.0, sD = (fl & SN_D1X) ? -1.0 : 1.0;
-    const double lN = lphi[0] * sN / fabs(D), lD = -lphi[0] * fabs(N) * sD / (D * D);
+    const double lN = lphi[0] * sN / By(fabs(D)), lD = -lphi[0] * fabs(N) * sD / By(D * D);
     lptr += lN + lD;
     lptl += lN + lD;
     lptc += -2.0 * lN + 2.0 * lD;
@@ -765,7 +800,7 @@ AF_HD void sensor_vjp(const double* c, const double* l, const double* r, const d
   {
     const double N = ptu - 2.0 * ptc + ptd, D = ptu + 2.0 * ptc + ptd;
     const double sN = (fl & SN_N1Y) ? -1.0 : 1.0, sD = (fl & SN_D1Y) ? -1.0 : 1.0;
-    const double lN = lphi[1] * sN / fabs(D), lD = -lphi[1] * fabs(N) * sD / (D * D);
+    const double lN = lphi[1] * sN / By(fabs(D)), lD = -lphi[1] * fabs(N) * sD / By(D * D);
     lptu += lN + lD;
     lptd += lN + lD;
     lptc += -2.0 * lN + 2.0 * lD;
@@ -776,32 +811,32 @@ AF_HD void sensor_vjp(const double* c, const double* l, const double* r, const d
   ptot_vjp(d, gm, lptd, ld);
   ptot_vjp(u, gm, lptu, lu);
   if (fl & SN_PHI2) {
-    const double divv = (r[1] / r[0] - l[1] / l[0]) / (2.0 * g.dx) + (u[2] / u[0] - d[2] / d[0]) / (2.0 * g.dy);
-    const double curlv = (r[2] / r[0] - l[2] / l[0]) / (2.0 * g.dx) - (u[1] / u[0] - d[1] / d[0]) / (2.0 * g.dy);
-    const double s = sqrt(divv * divv + curlv * curlv + SENSOR_TINY);
+    const double divv = (r[1] / By(r[0]) - l[1] / By(l[0])) / By(2.0 * g.dx) + (u[2] / By(u[0]) - d[2] / By(d[0])) / By(2.0 * g.dy);
+    const double curlv = (r[2] / By(r[0]) - l[2] / By(l[0])) / By(2.0 * g.dx) - (u[1] / By(u[0]) - d[1] / By(d[0])) / By(2.0 * g.dy);
+    const double s = root(divv * divv + curlv * curlv + SENSOR_TINY);
     const double lq = lphi[2];
-    const double ls = lq * divv / (s * s);
-    const double ldiv = -lq / s + ls * divv / s;
-    const double lcurl = ls * curlv / s;
+    const double ls = lq * divv / By(s * s);
+    const double ldiv = -lq / By(s) + ls * divv / By(s);
+    const double lcurl = ls * curlv / By(s);
     // velocity components v = m / rho of the neighbours
     auto addv = [](const double* U, int i, double lv, double* lU) {
-      lU[1 + i] += lv / U[0];
-      lU[0] -= lv * U[1 + i] / (U[0] * U[0]);
+      lU[1 + i] += lv / By(U[0]);
+      lU[0] -= lv * U[1 + i] / By(U[0] * U[0]);
     };
-    addv(r, 0, ldiv / (2.0 * g.dx), lr);
-    addv(l, 0, -ldiv / (2.0 * g.dx), ll);
-    addv(u, 1, ldiv / (2.0 * g.dy), lu);
-    addv(d, 1, -ldiv / (2.0 * g.dy), ld);
-    addv(r, 1, lcurl / (2.0 * g.dx), lr);
-    addv(l, 1, -lcurl / (2.0 * g.dx), ll);
-    addv(u, 0, -lcurl / (2.0 * g.dy), lu);
-    addv(d, 0, lcurl / (2.0 * g.dy), ld);
+    addv(r, 0, ldiv / By(2.0 * g.dx), lr);
+    addv(l, 0, -ldiv / By(2.0 * g.dx), ll);
+    addv(u, 1, ldiv / By(2.0 * g.dy), lu);
+    addv(d, 1, -ldiv / By(2.0 * g.dy), ld);
+    addv(r, 1, lcurl / By(2.0 * g.dx), lr);
+    addv(l, 1, -lcurl / By(2.0 * g.dx), ll);
+    addv(u, 0, -lcurl / By(2.0 * g.dy), lu);
+    addv(d, 0, lcurl / By(2.0 * g.dy), ld);
   }
   {  // phi3 = |N| / (|c4 + c5| + tiny)
     const double N = r[4] - l[4] + u[5] - d[5], s3 = c[4] + c[5];
     const double den = fabs(s3) + SENSOR_TINY;
     const double sN = (fl & SN_N3) ? -1.0 : 1.0, sS = (fl & SN_D3) ? -1.0 : 1.0;
-    const double lN = lphi[3] * sN / den, lden = -lphi[3] * fabs(N) / (den * den);
+    const double lN = lphi[3] * sN / By(den), lden = -lphi[3] * fabs(N) / By(den * den);
     lr[4] += lN;
     ll[4] -= lN;
     lu[5] += lN;
@@ -865,7 +900,7 @@ AF_HD void qcubic(const double* A1, const double* D, double r, double g, double 
   for (int c = 0; c < NV; ++c) W[c] = A1[c] + r * D[c];
   const double b2 = W[4] * W[4] + W[5] * W[5] + W[6] * W[6];
   const double m2 = W[1] * W[1] + W[2] * W[2] + W[3] * W[3];
-  const double e = W[7] - b2 / 2.0 - ep / (g - 1.0);
+  const double e = W[7] - b2 / 2.0 - ep / By(g - 1.0);
   q = W[0] * e - m2 / 2.0;
   const double de = D[7] - (W[4] * D[4] + W[5] * D[5] + W[6] * D[6]);
   dq = D[0] * e + W[0] * de - (W[1] * D[1] + W[2] * D[2] + W[3] * D[3]);
@@ -882,7 +917,7 @@ AF_HD double vroot(const double* A1, const double* D, double g, double ep) {
       lo = r;
     else
       hi = r;
-    double rn = r - q / dq;
+    double rn = r - q / By(dq);
     if (!(rn >= lo && rn <= hi)) rn = 0.5 * (lo + hi);
     const double step = fabs(rn - r);
     r = rn;
@@ -919,12 +954,30 @@ AF_HD void limiter_box(const double* A1, const double H[4][NV], double g, double
   for (int I = 0; I < 4; ++I) {
     Lr[I] = 1.0;
     if (H[I][0] < 0.0) {
-      const double f = (A1[0] - er) / (LAMBDA_REG - neg);
+      const double f = (A1[0] - er) / By(LAMBDA_REG - neg);
       if (f < 1.0) {
         Lr[I] = f;
         fl |= lm_lrf(I);
       }
     }
+  }
+  // Every vertex is a convex combination of A1 and the four points A1 + 4 Lr_I
+  // H_I (weights 1 - |K|/4 and 1/4) and the pressure is concave where rho > 0:
+  // when those five lie above eps_p by more than rounding can take (1e-12 of
+  // their energies) no vertex needs a root.
+  bool clear = A1[0] > 0.0;
+  double low = pres(A1, g), en = A1[7];
+  for (int I = 0; I < 4; ++I) {
+    double W[NV];
+    for (int c = 0; c < NV; ++c) W[c] = A1[c] + 4.0 * (Lr[I] * H[I][c]);
+    clear = clear && W[0] > 0.0;
+    low = dmin(low, pres(W, g));
+    en = dmax(en, W[7]);
+  }
+  if (clear && low >= ep + 1e-12 * en) {
+    for (int I = 0; I < 4; ++I) Lam[I] = Lr[I];
+    for (int k = 0; k < 15; ++k) rk[k] = 1.0;
+    return;
   }
   double rmin[4] = {1.0, 1.0, 1.0, 1.0};
   int arg[4] = {0, 0, 0, 0};
@@ -978,7 +1031,7 @@ AF_HD void limiter_box_vjp(const double* A1, const double H[4][NV], double g, do
   for (int I = 0; I < 4; ++I)
     if (fl & lm_neg(I)) neg += H[I][0];
   const double den = LAMBDA_REG - neg;
-  const double frac = (A1[0] - er) / den;
+  const double frac = (A1[0] - er) / By(den);
   double Lr[4], lLr[4];
   for (int I = 0; I < 4; ++I) {
     Lr[I] = (fl & lm_lrf(I)) ? frac : 1.0;
@@ -999,17 +1052,17 @@ AF_HD void limiter_box_vjp(const double* A1, const double H[4][NV], double g, do
     box_vertex(A1, H, Lr, k, D, W0);
     double W[NV];
     for (int c = 0; c < NV; ++c) W[c] = A1[c] + r * D[c];
-    const double e = W[7] - (W[4] * W[4] + W[5] * W[5] + W[6] * W[6]) / 2.0 - ep / (g - 1.0);
+    const double e = W[7] - (W[4] * W[4] + W[5] * W[5] + W[6] * W[6]) / 2.0 - ep / By(g - 1.0);
     const double qW[NV] = {e, -W[1], -W[2], -W[3], -W[0] * W[4], -W[0] * W[5], -W[0] * W[6], W[0]};
     double qr = 0.0;
     for (int c = 0; c < NV; ++c) qr += qW[c] * D[c];
-    const double s = -lr[k - 1] / qr;
+    const double s = -lr[k - 1] / By(qr);
     double lD[NV];
     for (int c = 0; c < NV; ++c) {
       lA1[c] += s * qW[c];
       lD[c] = s * r * qW[c];
     }
-    lep += s * (-W[0] / (g - 1.0));
+    lep += s * (-W[0] / By(g - 1.0));
     for (int I = 0; I < 4; ++I)
       if (k & (1 << I))
         for (int c = 0; c < NV; ++c) {
@@ -1020,9 +1073,9 @@ AF_HD void limiter_box_vjp(const double* A1, const double H[4][NV], double g, do
   double lneg = 0.0;
   for (int I = 0; I < 4; ++I)
     if (fl & lm_lrf(I)) {
-      lA1[0] += lLr[I] / den;
-      ler -= lLr[I] / den;
-      lneg += lLr[I] * frac / den;
+      lA1[0] += lLr[I] / By(den);
+      ler -= lLr[I] / By(den);
+      lneg += lLr[I] * frac / By(den);
     }
   for (int I = 0; I < 4; ++I)
     if (fl & lm_neg(I)) lH[I][0] += lneg;
@@ -1037,7 +1090,7 @@ struct CellIn {
   double Ss[NV], Sllf[NV];
 };
 AF_HD void cell_states(const CellIn& w, double dt, const AGeo& g, double* Allf, double* Asrc) {
-  const double ldx = dt / g.dx, ldy = dt / g.dy;
+  const double ldx = dt / By(g.dx), ldy = dt / By(g.dy);
   for (int c = 0; c < NV; ++c) {
     const double G = w.A[c] - ldx * (w.Fl[1][c] - w.Fl[0][c]) - ldy * (w.Fl[3][c] - w.Fl[2][c]);
     Allf[c] = G - dt * w.Sllf[c];
@@ -1045,7 +1098,7 @@ AF_HD void cell_states(const CellIn& w, double dt, const AGeo& g, double* Allf, 
   }
 }
 AF_HD void cell_H(const CellIn& w, double dt, const AGeo& g, double H[4][NV]) {
-  const double ldx = dt / g.dx, ldy = dt / g.dy;
+  const double ldx = dt / By(g.dx), ldy = dt / By(g.dy);
   for (int c = 0; c < NV; ++c) {
     H[0][c] = ldx * (w.Fs[0][c] - w.Fl[0][c]);
     H[1][c] = -ldx * (w.Fs[1][c] - w.Fl[1][c]);
@@ -1071,7 +1124,7 @@ AF_HD void cell_limiter(const CellIn& w, double dt, const AGeo& g, double& thsrc
   double th = 1.0;
   const double psrc = pres(Asrc, gm);
   if (psrc < ep) {
-    th = (pL - ep) / (pL - psrc);
+    th = (pL - ep) / By(pL - psrc);
     fl |= LM_TSRC;
   }
   uint32_t bf = 0;
@@ -1095,13 +1148,13 @@ struct CellAdj {
 AF_HD void cell_limiter_vjp(const CellIn& w, double dt, const AGeo& g, const double* rk, uint64_t fl,
                                   double lthsrc, const double* lLam, CellAdj& o) {
   const double gm = g.gamma;
-  const double ldx = dt / g.dx, ldy = dt / g.dy;
+  const double ldx = dt / By(g.dx), ldy = dt / By(g.dy);
   double Allf[NV], Asrc[NV];
   cell_states(w, dt, g, Allf, Asrc);
   const double rhoL = Allf[0], pL = pres(Allf, gm);
   const double er = (fl & LM_ER) ? rhoL : EPS_FLOOR, ep = (fl & LM_EP) ? pL : EPS_FLOOR;
   const double psrc = pres(Asrc, gm);
-  const double thr = (fl & LM_TSRC) ? (pL - ep) / (pL - psrc) : 1.0;
+  const double thr = (fl & LM_TSRC) ? (pL - ep) / By(pL - psrc) : 1.0;
   double th = thr;
   if (fl & LM_TS_ZERO)
     th = 0.0;
@@ -1126,7 +1179,7 @@ AF_HD void cell_limiter_vjp(const CellIn& w, double dt, const AGeo& g, const dou
   double lpL = 0.0, lrhoL = 0.0;
   if (fl & LM_TSRC) {
     const double den = pL - psrc;
-    const double ln = lth / den, ldn = -lth * thr / den;
+    const double ln = lth / By(den), ldn = -lth * thr / By(den);
     lpL += ln + ldn;
     lep -= ln;
     pres_vjp(Asrc, gm, -ldn, lAs);

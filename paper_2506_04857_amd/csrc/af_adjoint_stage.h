@@ -272,14 +272,14 @@ AF_HD void point_high(const AGeo& g, int kind, const PointSt& s, double dt, doub
     double Fd[NV], Fu[NV];
     flux(s.ca, g.gamma, 1, Fd);
     flux(s.cb, g.gamma, 1, Fu);
-    for (int c = 0; c < NV; ++c) R2[c] = (Fu[c] - Fd[c]) / g.dy;
-    d2 = (s.cb[5] - s.ca[5]) / g.dy;
+    for (int c = 0; c < NV; ++c) R2[c] = (Fu[c] - Fd[c]) / By(g.dy);
+    d2 = (s.cb[5] - s.ca[5]) / By(g.dy);
   } else if (kind == 1) {
     double Fl[NV], Fr[NV];
     flux(s.ca, g.gamma, 0, Fl);
     flux(s.cb, g.gamma, 0, Fr);
-    for (int c = 0; c < NV; ++c) R1[c] = (Fr[c] - Fl[c]) / g.dx;
-    d1 = (s.cb[4] - s.ca[4]) / g.dx;
+    for (int c = 0; c < NV; ++c) R1[c] = (Fr[c] - Fl[c]) / By(g.dx);
+    d1 = (s.cb[4] - s.ca[4]) / By(g.dx);
   }
   const double divB = d1 + d2;
   psi(s.U, P);
@@ -295,11 +295,18 @@ AF_HD void rec_point(const AGeo& g, const StateC& un, const StateC& u, const Tap
                      int l, double dt, double a, double b) {
   PointSt s;
   point_stencil(g, u, t, kind, k, l, s);
-  double H[NV], Lf[NV], W[NV];
+  double H[NV], W[NV];
   point_high(g, kind, s, dt, H);
-  point_llf(s.U, s.L, s.R, s.D, s.Up, dt, g, Lf);
   uint32_t fl = 0;
-  point_limit(H, Lf, g.gamma, W, fl);
+  if (H[0] >= EPS_FLOOR && pres(H, g.gamma) >= EPS_FLOOR) {
+    // both bounds are at most EPS_FLOOR, whatever the LLF state is: the
+    // limiter returns H
+    for (int c = 0; c < NV; ++c) W[c] = H[c];
+  } else {
+    double Lf[NV];
+    point_llf(s.U, s.L, s.R, s.D, s.Up, dt, g, Lf);
+    point_limit(H, Lf, g.gamma, W, fl);
+  }
   const size_t id = point_id(g, kind, k, l), n = point_n(g, kind);
   const double* unp = kind == 0 ? un.x : kind == 1 ? un.y : un.v;
   for (int c = 0; c < NV; ++c) out[id + c * n] = combine(a, b, unp[id + c * n], W[c]);
@@ -355,7 +362,7 @@ AF_HD void rec_iface(const AGeo& g, const StateC& u, const Tape& t, int dir, int
   flux(p[0], g.gamma, dir, Fa);
   flux(p[1], g.gamma, dir, Fb);
   flux(p[2], g.gamma, dir, Fc);
-  for (int c = 0; c < NV; ++c) Fh[c] = (Fa[c] + 4.0 * Fb[c] + Fc[c]) / 6.0;
+  for (int c = 0; c < NV; ++c) Fh[c] = (Fa[c] + 4.0 * Fb[c] + Fc[c]) / By(6.0);
   llf(Al, Ar, g.gamma, dir, Fl);
   if (dir == 0) {
     ldphi(e, t.phi, k - 1, j, pL);
@@ -421,7 +428,7 @@ AF_HD double div_bbar(const AGeo& g, const StateC& u, int i, int j) {
   ld(u.a, locA(g, i + 1, j), Ar);
   ld(u.a, locA(g, i, j - 1), Ad);
   ld(u.a, locA(g, i, j + 1), Au);
-  return (Ar[4] - Al[4]) / (2.0 * g.dx) + (Au[5] - Ad[5]) / (2.0 * g.dy);
+  return (Ar[4] - Al[4]) / By(2.0 * g.dx) + (Au[5] - Ad[5]) / By(2.0 * g.dy);
 }
 AF_HD void rec_limiter(const AGeo& g, const StateC& u, const Tape& t, int i, int j, double dt) {
   const Ext e = ext_of(g);
@@ -498,7 +505,7 @@ AF_HD void rec_update(const AGeo& g, const StateC& un, const StateC& u, const Ta
   cell_thetas(e, t, i, j, th, src);
   cell_sources(e, t, i, j, ts, Ss, Sllf);
   const double thsrc = t.thsrc[eidx(e, i, j)];
-  const double ldx = dt / g.dx, ldy = dt / g.dy;
+  const double ldx = dt / By(g.dx), ldy = dt / By(g.dy);
   const size_t id = (size_t)j * g.nx + i, n = (size_t)g.nx * g.ny;
   for (int c = 0; c < NV; ++c) {
     const double FL = th[0] * Fs[0][c] + (1.0 - th[0]) * Fl[0][c];
@@ -532,7 +539,7 @@ AF_HD void adj_update(const AGeo& g, const Tape& t, const AdjBuf& ab, const Stat
   for (int I = 0; I < 4; ++I) ld_iface(r[I], Fs[I], Fl[I], ts[I]);
   cell_thetas(e, t, i, j, th, src);
   cell_sources(e, t, i, j, ts, Ss, Sllf);
-  const double ldx = dt / g.dx, ldy = dt / g.dy;
+  const double ldx = dt / By(g.dx), ldy = dt / By(g.dy);
   const double coef[4] = {ldx, -ldx, ldy, -ldy};
   const size_t en = (size_t)e.ew * e.eh;
   for (int I = 0; I < 4; ++I) {
@@ -591,7 +598,7 @@ AF_HD void source_reverse(const AGeo& g, const Slot q[3][3], const double* lS) {
     }
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) {
-      dv[a][b] = d3(a, B1[0][b], B1[1][b], B1[2][b]) / g.dx + d3(b, B2[a][0], B2[a][1], B2[a][2]) / g.dy;
+      dv[a][b] = d3(a, B1[0][b], B1[1][b], B1[2][b]) / By(g.dx) + d3(b, B2[a][0], B2[a][1], B2[a][2]) / By(g.dy);
       double U[NV], Q[NV];
       ld(q[a][b].src, q[a][b].L, U);
       psi(U, Q);
@@ -609,8 +616,8 @@ AF_HD void source_reverse(const AGeo& g, const Slot q[3][3], const double* lS) {
       // this point is entry a of row b (B1 derivatives) and entry b of column a (B2)
       double l4 = 0.0, l5 = 0.0;
       for (int p = 0; p < 3; ++p) {
-        l4 += d3c(p, a) * ldv[p][b] / g.dx;
-        l5 += d3c(p, b) * ldv[a][p] / g.dy;
+        l4 += d3c(p, a) * ldv[p][b] / By(g.dx);
+        l5 += d3c(p, b) * ldv[a][p] / By(g.dy);
       }
       lU[4] += l4;
       lU[5] += l5;
@@ -694,10 +701,10 @@ AF_HD void adj_limiter(const AGeo& g, const StateC& u, const Tape& t, const AdjB
   put<Add>(lk.a, locA(g, i, j), lA);
   if (ldiv != 0.0) {
     const Loc Lr = locA(g, i + 1, j), Ll = locA(g, i - 1, j), Lu = locA(g, i, j + 1), Ld = locA(g, i, j - 1);
-    Add::add(lk.a + Lr.i + 4 * Lr.s, ldiv / (2.0 * g.dx));
-    Add::add(lk.a + Ll.i + 4 * Ll.s, -ldiv / (2.0 * g.dx));
-    Add::add(lk.a + Lu.i + 5 * Lu.s, ldiv / (2.0 * g.dy));
-    Add::add(lk.a + Ld.i + 5 * Ld.s, -ldiv / (2.0 * g.dy));
+    Add::add(lk.a + Lr.i + 4 * Lr.s, ldiv / By(2.0 * g.dx));
+    Add::add(lk.a + Ll.i + 4 * Ll.s, -ldiv / By(2.0 * g.dx));
+    Add::add(lk.a + Lu.i + 5 * Lu.s, ldiv / By(2.0 * g.dy));
+    Add::add(lk.a + Ld.i + 5 * Ld.s, -ldiv / By(2.0 * g.dy));
   }
   bool any = false;
   for (int c = 0; c < NV; ++c) any = any || lS[c] != 0.0;
@@ -736,8 +743,8 @@ AF_HD void adj_iface(const AGeo& g, const StateC& u, const Tape& t, const AdjBuf
   zero8(lAl);
   zero8(lAr);
   for (int c = 0; c < NV; ++c) {
-    lh[c] = lFh[c] / 6.0;
-    lh4[c] = 4.0 * lFh[c] / 6.0;
+    lh[c] = lFh[c] / By(6.0);
+    lh4[c] = 4.0 * lFh[c] / By(6.0);
   }
   flux_vjp(p[0], g.gamma, dir, lh, l0);
   flux_vjp(p[1], g.gamma, dir, lh4, l1);
@@ -832,7 +839,7 @@ AF_HD void line_scan(const Slot q[5], double gm, int n, double h, double& alpha,
     }
     b[m] = w[4 + n];
   }
-  dB = 0.5 * ((b[0] - 4.0 * b[1] + 3.0 * b[2]) / h + (-3.0 * b[2] + 4.0 * b[3] - b[4]) / h);
+  dB = 0.5 * ((b[0] - 4.0 * b[1] + 3.0 * b[2]) / By(h) + (-3.0 * b[2] + 4.0 * b[3] - b[4]) / By(h));
 }
 // Passes 2 and 3: the reverse of R = sum_m [sp_m F(w_m) + sd_m alpha w_m]
 // and of dB, one state at a time, then of alpha at its argmax.  The middle
@@ -845,7 +852,7 @@ AF_HD void line_reverse(const Slot q[5], double gm, int n, double h, double alph
   const double cm[5] = {0.0, 0.0, -3.0, 4.0, -1.0};
   double lal = 0.0;
   for (int m = 0; m < 5; ++m) {
-    const double sp = 0.5 * (cp[m] + cm[m]) / h, sd = 0.5 * (cp[m] - cm[m]) / h;
+    const double sp = 0.5 * (cp[m] + cm[m]) / By(h), sd = 0.5 * (cp[m] - cm[m]) / By(h);
     double w[NV], lF[NV], lw[NV];
     ld(q[m].src, q[m].L, w);
     for (int c = 0; c < NV; ++c) {
@@ -942,8 +949,8 @@ AF_HD void adj_point(const AGeo& g, const StateC& u, const Tape& t, const AdjBuf
   int mx = -1, my = -1;
   if (kind != 1) line_scan(lx, g.gamma, 0, g.dx, ax, mx, d1);
   if (kind != 0) line_scan(ly, g.gamma, 1, g.dy, ay, my, d2);
-  if (kind == 0) d2 = (pair[1].src[pair[1].L.i + 5 * pair[1].L.s] - pair[0].src[pair[0].L.i + 5 * pair[0].L.s]) / g.dy;
-  if (kind == 1) d1 = (pair[1].src[pair[1].L.i + 4 * pair[1].L.s] - pair[0].src[pair[0].L.i + 4 * pair[0].L.s]) / g.dx;
+  if (kind == 0) d2 = (pair[1].src[pair[1].L.i + 5 * pair[1].L.s] - pair[0].src[pair[0].L.i + 5 * pair[0].L.s]) / By(g.dy);
+  if (kind == 1) d1 = (pair[1].src[pair[1].L.i + 4 * pair[1].L.s] - pair[0].src[pair[0].L.i + 4 * pair[0].L.s]) / By(g.dx);
   const double divB = d1 + d2;
   {
     double U[NV], P[NV], lP[NV], lU[NV];
@@ -971,10 +978,10 @@ AF_HD void adj_point(const AGeo& g, const StateC& u, const Tape& t, const AdjBuf
         double w[NV], lF[NV], lw[NV];
         ld(pair[q].src, pair[q].L, w);
         const double sgnq = q ? 1.0 : -1.0;
-        for (int c = 0; c < NV; ++c) lF[c] = sgnq * lR[c] / h;
+        for (int c = 0; c < NV; ++c) lF[c] = sgnq * lR[c] / By(h);
         zero8(lw);
         flux_vjp(w, g.gamma, dir, lF, lw);
-        lw[4 + dir] += sgnq * ldiv / h;
+        lw[4 + dir] += sgnq * ldiv / By(h);
         slot_put<Add>(pair[q], lw);
       }
     }
