@@ -356,11 +356,8 @@ __device__ __forceinline__ void cells_tile(const Geo& g, CState u, const double*
     // the nine-point source: the point kernel's for the grid's cells; a ghost
     // cell across an outflow boundary (its mirrored stencil differs from its
     // image's) computes its own
-    if (!src || (g.bcx && (t.i < 0 || t.i >= g.nx)) || (g.bcy && (t.j < 0 || t.j >= g.ny))) {
-      double C[NV];
-      centre_value(g, u, t.i, t.j, C);
-      cell_source<double>(g, u, C, t.i, t.j, S);
-    }
+    if (!src || (g.bcx && (t.i < 0 || t.i >= g.nx)) || (g.bcy && (t.j < 0 || t.j >= g.ny)))
+      source_of_cell(g, u, t.i, t.j, S);
     double Fl[NV];
     cell_interface<0, CBX, CBY>(L, g, u, t, A, w0, Fl);
     // the right neighbour's flux: lane tx + 1 (the last column, whose update

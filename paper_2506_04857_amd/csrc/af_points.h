@@ -390,6 +390,135 @@ __device__ __forceinline__ PtPlace pt_place(const Geo& g, int bx, int by, int ti
   return t;
 }
 
+// ------------------------------------------------- centre value and source
+// The centre value and the nine-point source are formed by the point tile and,
+// where the cell tile does not wait for it, by the cell tile; their fused
+// multiply-adds are written out, so that both get the same bits.
+
+// One component of the unlimited centre value (Section 2.1): f, minus four times
+// the sum of the four face values; v, the sum of the four vertex values.
+__device__ __forceinline__ double centre_raw(double a, double f, double v) {
+#pragma clang fp contract(off)
+  return (fma(36.0, a, f) - v) * 0.0625;
+}
+
+// Psi of a state.
+__device__ __forceinline__ void psi_fma(const double U[NV], double P[NV]) {
+#pragma clang fp contract(off)
+  const double ri = rcp_r(U[0]);
+  P[0] = 0.0;
+  P[1] = U[4];
+  P[2] = U[5];
+  P[3] = U[6];
+  P[4] = U[1] * ri;
+  P[5] = U[2] * ri;
+  P[6] = U[3] * ri;
+  P[7] = fma(P[4], U[4], fma(P[5], U[5], P[6] * U[6]));
+}
+
+// source_nine of FP64.
+template <class BF, class PF>
+__device__ __forceinline__ void source_nine_fma(BF Bat, PF Psiat, double rdx, double rdy, double S[NV]) {
+#pragma clang fp contract(off)
+  double B1[3][3], B2[3][3];
+#pragma unroll
+  for (int b = 0; b < 3; ++b)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) Bat(a, b, B1[a][b], B2[a][b]);
+  auto d3 = [](int at, double u0, double u1, double u2) {
+#pragma clang fp contract(off)
+    return at == 0 ? fma(4.0, u1, fma(-3.0, u0, -u2)) : at == 1 ? u2 - u0 : fma(-4.0, u1, fma(3.0, u2, u0));
+  };
+  const double wq[3] = {1.0 / 6.0, 2.0 / 3.0, 1.0 / 6.0};
+  double f[9];
+#pragma unroll
+  for (int b = 0; b < 3; ++b)
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      f[3 * b + a] = (wq[a] * wq[b]) *
+                     fma(d3(a, B1[0][b], B1[1][b], B1[2][b]), rdx, d3(b, B2[a][0], B2[a][1], B2[a][2]) * rdy);
+#pragma unroll
+  for (int c = 0; c < NV; ++c) S[c] = 0.0;
+  // Three samples per trip: their loads are in flight together, while the
+  // states of all nine are never live together.
+#pragma unroll 3
+  for (int q = 0; q < 9; ++q) {
+    const int a = q % 3, b = q / 3;
+    double fq = f[0];
+#pragma unroll
+    for (int r = 1; r < 9; ++r) fq = q == r ? f[r] : fq;
+    double P[NV];
+    Psiat(a, b, P);
+#pragma unroll
+    for (int c = 1; c < NV; ++c) S[c] = fma(fq, P[c], S[c]);
+  }
+}
+
+// The nine-point source of cell (i,j) from the stage input.
+__device__ void source_of_cell(const Geo& g, CState u, int i, int j, double S[NV]) {
+  double C[NV];
+  {
+    double A[NV], Uc[NV], f[NV], w[NV], q[NV];
+    ldA(g, u.a, i, j, A);
+    ldX(g, u.x, i, j, f);
+    ldX(g, u.x, i + 1, j, w);
+    ldY(g, u.y, i, j, Uc);
+    ldY(g, u.y, i, j + 1, q);
+#pragma unroll
+    for (int c = 0; c < NV; ++c) f[c] = -4.0 * ((f[c] + w[c]) + (Uc[c] + q[c]));
+    ldV(g, u.v, i, j, Uc);
+    ldV(g, u.v, i + 1, j, w);
+#pragma unroll
+    for (int c = 0; c < NV; ++c) Uc[c] += w[c];
+    ldV(g, u.v, i, j + 1, q);
+    ldV(g, u.v, i + 1, j + 1, w);
+#pragma unroll
+    for (int c = 0; c < NV; ++c) Uc[c] = centre_raw(A[c], f[c], Uc[c] + (q[c] + w[c]));
+    limit_centre(Uc, A, g.gm1, C, nullptr, false);
+  }
+  auto at = [&](int a, int b, const double*& base, long& plane, long& off) {
+    const int aa = a >> 1, bb = b >> 1;
+    if (b == 1) {
+      base = u.x;
+      plane = g.sx;
+      off = (long)map_cell(j, g.ny, g.bcy) * g.nxp + map_node(i + aa, g.nx, g.bcx);
+    } else if (a == 1) {
+      base = u.y;
+      plane = g.sy;
+      off = (long)map_node(j + bb, g.ny, g.bcy) * g.nx + map_cell(i, g.nx, g.bcx);
+    } else {
+      base = u.v;
+      plane = g.sv;
+      off = (long)map_node(j + bb, g.ny, g.bcy) * g.nxp + map_node(i + aa, g.nx, g.bcx);
+    }
+  };
+  auto Bat = [&](int a, int b, double& b1, double& b2) {
+    if (a == 1 && b == 1) {
+      b1 = C[4];
+      b2 = C[5];
+      return;
+    }
+    const double* base;
+    long plane, off;
+    at(a, b, base, plane, off);
+    b1 = base[4 * plane + off];
+    b2 = base[5 * plane + off];
+  };
+  auto Psiat = [&](int a, int b, double P[NV]) {
+    if (a == 1 && b == 1) {
+      psi_fma(C, P);
+      return;
+    }
+    const double* base;
+    long plane, off;
+    at(a, b, base, plane, off);
+    double w[NV];
+    load8(base, plane, off, w);
+    psi_fma(w, P);
+  };
+  source_nine_fma(Bat, Psiat, g.rdx, g.rdy, S);
+}
+
 // The unlimited centre value of the thread's cell from the tile's states and
 // its average A.  The pins keep the eight samples from being loaded all at
 // once.
@@ -414,7 +543,7 @@ __device__ __forceinline__ void tile_centre(double (*s)[PB][PB], const PtPlace& 
   lds8(s, SV_, t.tyu, t.tx, q);
   lds8(s, SV_, t.tyu, t.txr, w);
 #pragma unroll
-  for (int c = 0; c < NV; ++c) Uc[c] = (36.0 * A[c] + f[c] - (Uc[c] + (q[c] + w[c]))) * 0.0625;
+  for (int c = 0; c < NV; ++c) Uc[c] = centre_raw(A[c], f[c], Uc[c] + (q[c] + w[c]));
 }
 
 // The nine-point source of the thread's cell from the tile's point values and
@@ -434,16 +563,16 @@ __device__ __forceinline__ void tile_source(double (*s)[PB][PB], const Geo& g, c
   };
   auto Psiat = [&](int a, int b, double P[NV]) {
     if (a == 1 && b == 1) {
-      psi(C, P);
+      psi_fma(C, P);
       return;
     }
     const int base = b == 1 ? SX_ : (a == 1 ? SY_ : SV_);
     double w[NV];
     lds8(s, base, b == 2 ? t.tyu : t.ty, a == 2 ? t.txr : t.tx, w);
-    psi(w, P);
+    psi_fma(w, P);
   };
   double S[NV];
-  source_nine<double>(Bat, Psiat, g.rdx, g.rdy, S);
+  source_nine_fma(Bat, Psiat, g.rdx, g.rdy, S);
 #pragma unroll
   for (int c = 0; c < NV; ++c) src[c * g.sc] = S[c];
 }

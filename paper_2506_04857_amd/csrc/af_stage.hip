@@ -3,7 +3,8 @@
 // declared in include/af_mhd.h.
 //
 // A stage (forward Euler on U^(k), then out = a_k U^n + b_k FE) is two
-// launches that read only U^(k) (and U^n for the combination):
+// launches (one where all tiles run at once, k_stage) that read only U^(k) (and
+// U^n for the combination):
 //   k_points  point values (Section 2.3): centre values (Section 2.1,
 //             remark rmk:cell_center), LLF flux-vector splitting with the
 //             central div B source, first-order LLF safe state and scaling
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(point_threads<R>(), point_waves<R>()) void k_points
     double cb, Counters* cn, int ntx, int nty, double* __restrict__ wpart) {
   __shared__ R s[point_fields<R>()][PB][PB];
   int bx, by;
-  if (!xcd_tile(ntx, nty, bx, by)) {
+  if (!xcd_tile((int)blockIdx.x, ntx, nty, bx, by)) {
     if (WDT && threadIdx.x == 0) wpart[blockIdx.x] = 0.0;
     return;
   }
@@ -71,11 +72,57 @@ __global__ __launch_bounds__(CBX0 * CBY0) void k_cells(Geo g, CState u, const do
                                                        double* __restrict__ wpart) {
   __shared__ CellsTileLDS<R, CBX0, CBY0> L;
   int bx, by;
-  if (!xcd_tile(ntx, nty, bx, by)) {
+  if (!xcd_tile((int)blockIdx.x, ntx, nty, bx, by)) {
     if (WDT && threadIdx.x == 0) wpart[blockIdx.x] = 0.0;
     return;
   }
   cells_tile_any<R, CBX0, CBY0>(g, u, src, un, out, *dtp, ca, cb, cn, bx, by, L, WDT ? wpart + blockIdx.x : nullptr);
+}
+
+// A stage of FP64 in one launch, for grids whose tiles all run at once: the
+// first gridDim.x - pwg workgroups take cell tiles, the last pwg point tiles
+// (two bands as of xcd_tile, each a multiple of 8 workgroups).  The cell tiles
+// form their cells' nine-point sources from the stage input, so that the two
+// kinds share nothing within the launch.  On such a grid a launch lasts as long
+// as one tile (a chain of dependent loads, divisions and barriers), not as long
+// as its work: in two launches the two chains and the second's start follow
+// each other.  32^2: 11.7 + 15.5 us and a gap in two launches, 23 us in one (a
+// step 84.9 -> 74.6 us); 200 x 137 (227 tiles): 17.0 + 24.7 us, 31 us in one (dt
+// and three stages 126 -> 93 us).
+constexpr int STAGE_THREADS = fp64::PNT;
+template <bool WDT>
+__global__ __launch_bounds__(STAGE_THREADS) void k_stage(Geo g, CState u, CState un, MState out, MState stash,
+                                                         const double* dtp, double ca, double cb, Counters* cn,
+                                                         int ptx, int pty, int ctx, int cty, int pwg,
+                                                         double* __restrict__ wpart) {
+  static_assert(CBX0 * CBY0 == STAGE_THREADS, "a tile of either kind takes the whole workgroup");
+  union Lds {
+    double pts[point_fields<double>()][PB][PB];
+    CellsTileLDS<double, CBX0, CBY0> cells;
+  };
+  __shared__ Lds L;
+  const int b = (int)blockIdx.x, cwg = (int)gridDim.x - pwg;
+  double* const wslot = WDT ? wpart + b : nullptr;
+  int bx, by;
+  if (b < cwg) {
+    if (xcd_tile(b, ctx, cty, bx, by)) {
+      cells_tile_any<double, CBX0, CBY0>(g, u, nullptr, un.a, out.a, *dtp, ca, cb, cn, bx, by, L.cells, wslot);
+      return;
+    }
+  } else if (xcd_tile(b - cwg, ptx, pty, bx, by)) {
+    points_tile<double>(g, u, un, out, stash, nullptr, *dtp, ca, cb, cn, bx, by, L.pts, wslot);
+    return;
+  }
+  if (WDT && threadIdx.x == 0) *wslot = 0.0;
+}
+
+// Whether a stage's tiles all run at once in one launch: a workgroup of k_stage
+// takes a CU's LDS, and there are 256.  With one tile more, the launch is two
+// rounds of tiles that compute the sources besides, and so are the two launches
+// (the point tiles run two to a CU there).
+constexpr int STAGE_MAX_TILES = 256;
+inline bool one_launch(const Geo& g) {
+  return (long)points_tiles_x(g) * points_tiles_y(g) + (long)cells_tiles_x(g) * cells_tiles_y(g) <= STAGE_MAX_TILES;
 }
 
 __global__ __launch_bounds__(BLK) void k_dt_partial(Geo g, CState u, double* partial) {
@@ -435,6 +482,12 @@ int run_stage(af_mhd_ctx* c, int k, const af_mhd_state* un, const af_mhd_state* 
   const MState st{o.a, o.x == n.x ? sc[1] : o.x, o.y == n.y ? sc[2] : o.y, o.v == n.v ? sc[3] : o.v};
   const int ptx = points_tiles_x(g), pty = points_tiles_y(g);
   double* const wcells = wpart ? wpart + xcd_grid(ptx, pty) : nullptr;
+  if (!c->f32 && !c->timer && one_launch(g)) {  // a timed context keeps the two kinds apart
+    const int ctx = cells_tiles_x(g), cty = cells_tiles_y(g), pwg = xcd_grid(ptx, pty);
+    (wpart ? k_stage<true> : k_stage<false>)<<<pwg + xcd_grid(ctx, cty), STAGE_THREADS, 0, s>>>(
+        g, u, n, o, st, dt_dev, A[k], B[k], c->ws.cnt, ptx, pty, ctx, cty, pwg, wpart);
+    return check_hip(c, "stage launch");
+  }
   hipEvent_t end;
   hipError_t e = timer_begin(c, KernelTimer::POINTS, &end);
   if (e != hipSuccess) return fail(c, AF_EHIP, hipGetErrorString(e));

@@ -19,9 +19,8 @@ constexpr int BLK = 256;
 // row-major order and the halos its tiles share stay in its L2.  Returns
 // false for the padding workgroups of the last band.
 constexpr int NXCD = 8;
-__device__ __forceinline__ bool xcd_tile(int ntx, int nty, int& bx, int& by) {
+__device__ __forceinline__ bool xcd_tile(int b, int ntx, int nty, int& bx, int& by) {
   const int n = ntx * nty, per = (n + NXCD - 1) / NXCD;
-  const int b = (int)blockIdx.x;
   const int t = (b % NXCD) * per + b / NXCD;
   if (t >= n) return false;
   bx = t % ntx;
