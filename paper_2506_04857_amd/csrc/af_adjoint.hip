@@ -6,9 +6,9 @@
 // cell, update cell); launches run in dependency order on the context's
 // stream.  The reverse sweep scatters with hardware FP64 atomics into the
 // adjoint states and into the intermediate adjoint buffers of the
-// workspace (the centre's adjoint is gathered by the points instead), so
-// its sums are order-dependent at the rounding level (not bitwise
-// reproducible run to run).
+// workspace (the centre's adjoint and, on larger grids, the points' lines are
+// gathered instead), so its sums are order-dependent at the rounding level (not
+// bitwise reproducible run to run).
 // No contraction of a*b+c into fused multiply-adds in this translation unit
 // (it must precede the includes to cover the entity functions): the
 // recording forward and the reverse sweep then round like the FP64 oracle,
@@ -135,6 +135,35 @@ __global__ __launch_bounds__(ABLK) void ka_points(AGeo g, StateC u, Tape t, AdjB
   if (!point_of(g, gtid(), kind, k, l)) return;
   adj_point<DevAdd>(g, u, t, ab, lo, ln, lk, kind, k, l, *dt, a, b);
 }
+// At most LIMITED_GRID workgroups, a wave per SIMD, which is what its registers
+// admit: mostly it only reads the decisions (a workgroup per 256 points queues
+// for registers beside the cells' kernels: 60 us where this takes 8).
+constexpr int LIMITED_GRID = 256;
+__global__ __launch_bounds__(ABLK) void ka_limited(AGeo g, StateC u, Tape t, AdjBuf ab, StateC lo, StateM lk,
+                                                   const double* dt, double b) {
+  int kind, k, l;
+  for (long q = gtid(); point_of(g, q, kind, k, l); q += (long)gridDim.x * ABLK)
+    adj_point_limited<DevAdd>(g, u, t, ab, lo, lk, kind, k, l, *dt, b);
+}
+__global__ __launch_bounds__(ABLK) void ka_lines(AGeo g, StateC u, Tape t, AdjBuf ab, StateC lo, StateM ln, StateM lk,
+                                                 const double* dt, double a, double b) {
+  int kind, k, l;
+  if (!point_of(g, gtid(), kind, k, l)) return;
+  adj_point_lines<DevAdd>(g, u, t, ab, lo, ln, lk, kind, k, l, *dt, a, b);
+}
+__global__ __launch_bounds__(ABLK) void ka_lines_gather(AGeo g, StateC u, Tape t, AdjBuf ab, StateM lk,
+                                                        const double* dt) {
+  int kind, k, l;
+  const long cells = (long)g.nx * g.ny, q = gtid();
+  if (q < cells) {
+    kind = 3;
+    k = (int)(q % g.nx);
+    l = (int)(q / g.nx);
+  } else if (!point_of(g, q - cells, kind, k, l)) {
+    return;
+  }
+  adj_lines_gather<DevAdd>(g, u, t, ab, lk, kind, k, l, *dt);
+}
 __global__ __launch_bounds__(ABLK) void ka_centre(AGeo g, StateC u, Tape t, AdjBuf ab, StateM lk) {
   const long q = gtid();
   if (q >= (long)g.nx * g.ny) return;
@@ -181,6 +210,23 @@ bool same_state(const af_mhd_state* a, const af_mhd_state* b) {
   return a->cell == b->cell || a->xface == b->xface || a->yface == b->yface || a->vert == b->vert;
 }
 
+// Points (X, Y and V together) up to which their reverse is one launch that
+// scatters, beyond it three that gather.  On a small grid a launch lasts as long
+// as one point's chain, so that one is shorter than three; on a large one the
+// atomic additions bound the scatter.  Gradients of three steps on one stream,
+// scatter / gather: Alfven wave 64^2 1432 / 1514 us, 128^2 1521 / 1520, 160^2
+// (77 thousand) 1907 / 1753, 256^2 3560 / 3171, 512^2 11631 / 9955; shock 128^2
+// 1816 / 2085, 160^2 2263 / 2323, 200^2 2752 / 2692, 512^2 12123 / 11096.
+constexpr long SCATTER_POINTS = 64000;
+// Points up to which a stage's kernels all run on the context's stream.  Beyond
+// it the points' run on an auxiliary stream beside the cells': that costs two or
+// three waits from stream to stream a stage, some 10 us each, and gains where the
+// kernels outlast them.  One stream / two: Alfven wave 64^2 1432 / 2092 us, 200^2
+// (120 thousand points) 2182 / 2693, 256^2 3171 / 3211, 512^2 9955 / 9311; shock
+// 200^2 2692 / 2916, 256^2 4043 / 3621, 512^2 11096 / 9958.
+constexpr long ONE_STREAM_POINTS = 160000;
+long points_of(const AGeo& g) { return (long)g.nxp * g.ny + (long)g.nx * g.nyp + (long)g.nxp * g.nyp; }
+
 const double RK_A[3] = {0.0, 0.75, 1.0 / 3.0};
 const double RK_B[3] = {1.0, 0.25, 2.0 / 3.0};
 
@@ -193,11 +239,23 @@ struct af_mhd_adj {
   size_t ab_doubles;
   size_t tape_bytes;
   hipStream_t stream;
-  // The reverse of the point update runs on an auxiliary stream beside the
-  // reverse of the cell update: the two only add into the shared adjoint
-  // buffers (atomics), and the centre kernels that read them wait for both.
+  // On large grids (ONE_STREAM_POINTS) the point update and its reverse run on
+  // an auxiliary stream beside the cell update and its reverse: the two reverse
+  // sides only add into the shared adjoint buffers (atomics), and the centre
+  // kernels that read them wait for both.  Null elsewhere: all on `stream`.
   hipStream_t aux = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
+  // The points' stream.
+  hipStream_t side() const { return aux ? aux : stream; }
+  // What is enqueued on the points' stream from here on waits for the
+  // context's, and the other way round.
+  hipError_t fork_now() {
+    if (!aux) return hipSuccess;
+    const hipError_t e = hipEventRecord(fork, stream);
+    return e == hipSuccess ? hipStreamWaitEvent(aux, fork, 0) : e;
+  }
+  hipError_t join_record() { return aux ? hipEventRecord(join, aux) : hipSuccess; }
+  hipError_t join_wait() { return aux ? hipStreamWaitEvent(stream, join, 0) : hipSuccess; }
   std::string err;
   ~af_mhd_adj() {
     if (fork) (void)hipEventDestroy(fork);
@@ -243,14 +301,16 @@ int af_mhd_adj_init(const af_mhd_params* p, void* workspace_dev, size_t workspac
   af_mhd_adj* c = new (std::nothrow) af_mhd_adj();
   if (!c) return adj_init_err = "af_mhd_adj_init: out of host memory", AF_EINVAL;
   c->g = g;
-  adjbuf_layout(g, static_cast<char*>(workspace_dev), &c->ab);
+  size_t zeroed = 0;
+  adjbuf_layout(g, static_cast<char*>(workspace_dev), &c->ab, &zeroed);
   c->ab_base = static_cast<double*>(workspace_dev);
-  c->ab_doubles = need / sizeof(double);
+  c->ab_doubles = zeroed / sizeof(double);
   c->tape_bytes = tape_layout(g, nullptr, nullptr);
   c->stream = static_cast<hipStream_t>(hip_stream);
-  hipError_t e = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->join, hipEventDisableTiming);
+  const bool two = points_of(g) > ONE_STREAM_POINTS;
+  hipError_t e = two ? hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) : hipSuccess;
+  if (two && e == hipSuccess) e = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming);
+  if (two && e == hipSuccess) e = hipEventCreateWithFlags(&c->join, hipEventDisableTiming);
   if (e != hipSuccess) {
     adj_init_err = std::string("af_mhd_adj_init: ") + hipGetErrorString(e);
     delete c;
@@ -278,20 +338,18 @@ int af_mhd_adj_record(af_mhd_adj* c, int k, const af_mhd_state* un, const af_mhd
   hipStream_t s = c->stream;
   (void)hipGetLastError();
   kr_centre<<<nblk((long)g.nx * g.ny), ABLK, 0, s>>>(g, u, t);
-  // fork: the points need only the centre values; they run on the
-  // auxiliary stream beside the cell chain (disjoint outputs and tape fields)
-  hipError_t he = hipEventRecord(c->fork, s);
-  if (he == hipSuccess) he = hipStreamWaitEvent(c->aux, c->fork, 0);
+  // the points need only the centre values and go beside the cell chain
+  // (disjoint outputs and tape fields)
+  hipError_t he = c->fork_now();
   if (he != hipSuccess) return fail(c, AF_EHIP, std::string("af_mhd_adj_record: ") + hipGetErrorString(he));
-  kr_points<<<nblk((long)g.nxp * g.ny + (long)g.nx * g.nyp + (long)g.nxp * g.nyp), ABLK, 0, c->aux>>>(
-      g, n, u, t, o, dt_dev, a, b);
-  he = hipEventRecord(c->join, c->aux);
+  kr_points<<<nblk(points_of(g)), ABLK, 0, c->side()>>>(g, n, u, t, o, dt_dev, a, b);
+  he = c->join_record();
   kr_sensor<<<nblk((long)e.sw * e.sh), ABLK, 0, s>>>(g, u, t);
   kr_iface<<<nblk((long)e.xw * e.xh + (long)e.yw * e.yh), ABLK, 0, s>>>(g, u, t);
   kr_limiter<<<nblk((long)e.ew * e.eh), ABLK, 0, s>>>(g, u, t, dt_dev);
   kr_update<<<nblk((long)g.nx * g.ny), ABLK, 0, s>>>(g, n, u, t, o.a, dt_dev, a, b);
-  // join: the stage's output and tape are complete on s
-  if (he == hipSuccess) he = hipStreamWaitEvent(s, c->join, 0);
+  // the stage's output and tape are complete on s
+  if (he == hipSuccess) he = c->join_wait();
   if (he != hipSuccess) return fail(c, AF_EHIP, std::string("af_mhd_adj_record: ") + hipGetErrorString(he));
   return check_hip(c, "af_mhd_adj_record");
 }
@@ -314,24 +372,36 @@ int af_mhd_adj_stage(af_mhd_adj* c, int k, const af_mhd_state* uk, const void* t
   const double a = RK_A[k], b = RK_B[k];
   hipStream_t s = c->stream;
   (void)hipGetLastError();
+  // the points' reverse beside the cells'
+  const long points = points_of(g);
+  const bool gather = points > SCATTER_POINTS;
+  const hipStream_t side = c->side();
+  hipError_t he = hipSuccess;
+  if (gather) {  // only the last of the three needs the zeroed buffers
+    he = c->fork_now();
+    if (he != hipSuccess) return fail(c, AF_EHIP, std::string("af_mhd_adj_stage: ") + hipGetErrorString(he));
+    ka_limited<<<nblk(points) < LIMITED_GRID ? nblk(points) : LIMITED_GRID, ABLK, 0, side>>>(g, u, t, c->ab, lo, lk,
+                                                                                           dt_dev, b);
+  }
   ka_zero<<<nblk((long)c->ab_doubles) < 4096 ? nblk((long)c->ab_doubles) : 4096, ABLK, 0, s>>>(c->ab_base,
                                                                                                 (long)c->ab_doubles);
-  // fork: the points' reverse on the auxiliary stream, the cells' on s
-  hipError_t he = hipEventRecord(c->fork, s);
-  if (he == hipSuccess) he = hipStreamWaitEvent(c->aux, c->fork, 0);
+  if (gather) ka_lines<<<nblk(points), ABLK, 0, side>>>(g, u, t, c->ab, lo, ln, lk, dt_dev, a, b);
+  he = c->fork_now();
   if (he != hipSuccess) return fail(c, AF_EHIP, std::string("af_mhd_adj_stage: ") + hipGetErrorString(he));
-  ka_points<<<nblk((long)g.nxp * g.ny + (long)g.nx * g.nyp + (long)g.nxp * g.nyp), ABLK, 0, c->aux>>>(
-      g, u, t, c->ab, lo, ln, lk, dt_dev, a, b);
-  he = hipEventRecord(c->join, c->aux);
+  if (gather)
+    ka_lines_gather<<<nblk(points + (long)g.nx * g.ny), ABLK, 0, side>>>(g, u, t, c->ab, lk, dt_dev);
+  else
+    ka_points<<<nblk(points), ABLK, 0, side>>>(g, u, t, c->ab, lo, ln, lk, dt_dev, a, b);
+  he = c->join_record();
   ka_update<<<nblk((long)g.nx * g.ny), ABLK, 0, s>>>(g, t, c->ab, lo, ln, lk, dt_dev, a, b);
   ka_limiter<<<nblk((long)e.ew * e.eh), ABLK, 0, s>>>(g, u, t, c->ab, lk, dt_dev);
   ka_iface<<<nblk((long)e.xw * e.xh + (long)e.yw * e.yh), ABLK, 0, s>>>(g, u, t, c->ab, lk);
   ka_sensor<<<nblk((long)e.sw * e.sh), ABLK, 0, s>>>(g, u, t, c->ab, lk);
-  // join: the centre kernels read what both sides added
-  if (he == hipSuccess) he = hipStreamWaitEvent(s, c->join, 0);
+  // the centre kernels read what both sides added
+  if (he == hipSuccess) he = c->join_wait();
   if (he != hipSuccess) return fail(c, AF_EHIP, std::string("af_mhd_adj_stage: ") + hipGetErrorString(he));
   ka_centre<<<nblk((long)g.nx * g.ny), ABLK, 0, s>>>(g, u, t, c->ab, lk);
-  ka_centre_gather<<<nblk((long)g.nxp * g.ny + (long)g.nx * g.nyp + (long)g.nxp * g.nyp), ABLK, 0, s>>>(g, c->ab, lk);
+  ka_centre_gather<<<nblk(points), ABLK, 0, s>>>(g, c->ab, lk);
   return check_hip(c, "af_mhd_adj_stage");
 }
 

@@ -63,6 +63,11 @@ struct AdjBuf {
   double* lth;   // [ne]
   double* lSs;   // [8][ne]
   double* lSll;  // [8][ne]
+  // What the lines through the points X, Y, V hand to the gather (see
+  // adj_point_lines); every entry is written before it is read.
+  double* pH[3];    // [8][points] adjoint of the high-order state
+  double* pq[3];    // [6][points] adjoint of div B, div B; alpha and its adjoint of the x line, of the y line
+  uint32_t* pm[3];  // [points] slot of the largest spectral radius, plus one: x line | y line << 3
 };
 
 struct Sizes {
@@ -116,7 +121,8 @@ inline size_t tape_layout(const AGeo& g, char* base, Tape* t) {
   if (t) *t = x;
   return off;
 }
-inline size_t adjbuf_layout(const AGeo& g, char* base, AdjBuf* a) {
+// zeroed: the bytes, from the start, that a sweep begins with zeros in.
+inline size_t adjbuf_layout(const AGeo& g, char* base, AdjBuf* a, size_t* zeroed = nullptr) {
   const Sizes s = sizes_of(g);
   size_t off = 0;
   auto take = [&](size_t n) -> double* {
@@ -137,6 +143,12 @@ inline size_t adjbuf_layout(const AGeo& g, char* base, AdjBuf* a) {
   x.lth = take(s.ne);
   x.lSs = take(8 * s.ne);
   x.lSll = take(8 * s.ne);
+  if (zeroed) *zeroed = off;
+  for (int q = 0; q < 3; ++q) {
+    x.pH[q] = take(8 * s.set[q + 1]);
+    x.pq[q] = take(6 * s.set[q + 1]);
+    x.pm[q] = (uint32_t*)take((s.set[q + 1] + 1) / 2);
+  }
   if (a) *a = x;
   return off;
 }
@@ -986,6 +998,225 @@ AF_HD void adj_point(const AGeo& g, const StateC& u, const Tape& t, const AdjBuf
       }
     }
   }
+}
+
+// ------------------------------------- the points' reverse without scatters
+// adj_point scatters each point's two lines to their states, some 200 atomic
+// additions a cell.  The flux's transposed Jacobian is linear, so that a sweep
+// can gather instead: adj_point_lines leaves each point's line quantities,
+// adj_lines_gather sums, for one DoF and direction, what the lines that hold
+// it pass to its flux, and applies the transposed Jacobian once (two of them a
+// DoF instead of up to eighteen).  Where the scaling limiter acted,
+// adj_point_limited comes first (rare; apart, because its registers would
+// bring every point down to one wave per SIMD).  What bounds either form is
+// memory latency and, the scatter, the atomic additions (with plain stores in
+// their place ka_points took 100 us instead of 169).  256^2, beside the cells'
+// kernels: ka_points 169 us; ka_limited 8, ka_lines 30, ka_lines_gather 55 us, and
+// the cells' kernels, which add to the same memory, ka_limiter 98 -> 50, ka_iface
+// 78 -> 60 us.
+template <class Add>
+AF_HD void adj_point_limited(const AGeo& g, const StateC& u, const Tape& t, const AdjBuf& ab, const StateC& lo,
+                             const StateM& lk, int kind, int k, int l, double dt, double b) {
+  const size_t id = point_id(g, kind, k, l), n = point_n(g, kind);
+  const uint32_t fl = t.pfl[kind][id];
+  if (!(fl & (BL_T1 | BL_T2 | BL_SHIFT | BL_ZERO))) return;
+  const double* lop = kind == 0 ? lo.x : kind == 1 ? lo.y : lo.v;
+  double lam[NV], lH[NV];
+  bool any = false;
+  for (int c = 0; c < NV; ++c) {
+    lam[c] = b * lop[id + c * n];
+    any = any || lam[c] != 0.0;
+  }
+  zero8(lH);
+  if (any) point_limited_vjp<Add>(g, u, t, lk, kind, k, l, dt, fl, lam, lH);
+  st8(ab.pH[kind], id, n, lH);
+}
+
+// line_scan, and the fourth difference w0 - 4w1 + 6w2 - 4w3 + w4 that alpha
+// multiplies.
+AF_HD void line_scan4(const Slot q[5], double gm, int n, double h, double& alpha, int& am, double& dB, double* d4) {
+  const double co[5] = {1.0, -4.0, 6.0, -4.0, 1.0};
+  alpha = 0.0;
+  am = -1;
+  double b[5];
+  zero8(d4);
+  for (int m = 0; m < 5; ++m) {
+    double w[NV];
+    ld(q[m].src, q[m].L, w);
+    const double r = srad(w, gm, n);
+    if (alpha < r) {
+      alpha = r;
+      am = m;
+    }
+    b[m] = w[4 + n];
+    for (int c = 0; c < NV; ++c) d4[c] += co[m] * w[c];
+  }
+  dB = 0.5 * ((b[0] - 4.0 * b[1] + 3.0 * b[2]) / By(h) + (-3.0 * b[2] + 4.0 * b[3] - b[4]) / By(h));
+}
+
+// Point of kind (0 X, 1 Y, 2 V): its share of lam_n, and its line quantities.
+template <class Add>
+AF_HD void adj_point_lines(const AGeo& g, const StateC& u, const Tape& t, const AdjBuf& ab, const StateC& lo,
+                           const StateM& ln, const StateM& lk, int kind, int k, int l, double dt, double a, double b) {
+  const size_t id = point_id(g, kind, k, l), n = point_n(g, kind);
+  const double* lop = kind == 0 ? lo.x : kind == 1 ? lo.y : lo.v;
+  double* lnp = kind == 0 ? ln.x : kind == 1 ? ln.y : ln.v;
+  double lH[NV], qv[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  uint32_t pm = 0;
+  bool any = false;
+  for (int c = 0; c < NV; ++c) {
+    const double x = lop[id + c * n];
+    if (a != 0.0 && x != 0.0) Add::add(lnp + id + c * n, a * x);
+    lH[c] = b * x;
+    any = any || lH[c] != 0.0;
+  }
+  if (t.pfl[kind][id] & (BL_T1 | BL_T2 | BL_SHIFT | BL_ZERO))
+    ld8(ab.pH[kind], id, n, lH);
+  else
+    st8(ab.pH[kind], id, n, lH);  // limiter inactive: the output is U^H
+  if (any) {
+    Slot lx[5], ly[5], pair[2];
+    point_slots(g, u, t, ab, lk, kind, k, l, lx, ly, pair);
+    double d1 = 0.0, d2 = 0.0, d4[NV];
+    int am;
+    if (kind != 1) {
+      line_scan4(lx, g.gamma, 0, g.dx, qv[2], am, d1, d4);
+      double s = 0.0;
+      for (int c = 0; c < NV; ++c) s += lH[c] * d4[c];
+      qv[3] = -dt * s * 0.5 / By(g.dx);
+      pm |= (uint32_t)(am + 1);
+    }
+    if (kind != 0) {
+      line_scan4(ly, g.gamma, 1, g.dy, qv[4], am, d2, d4);
+      double s = 0.0;
+      for (int c = 0; c < NV; ++c) s += lH[c] * d4[c];
+      qv[5] = -dt * s * 0.5 / By(g.dy);
+      pm |= (uint32_t)(am + 1) << 3;
+    }
+    if (kind == 0) d2 = (pair[1].src[pair[1].L.i + 5 * pair[1].L.s] - pair[0].src[pair[0].L.i + 5 * pair[0].L.s]) / By(g.dy);
+    if (kind == 1) d1 = (pair[1].src[pair[1].L.i + 4 * pair[1].L.s] - pair[0].src[pair[0].L.i + 4 * pair[0].L.s]) / By(g.dx);
+    const double* src = kind == 0 ? u.x : kind == 1 ? u.y : u.v;
+    double U[NV], P[NV];
+    ld(src, Loc{id, n}, U);
+    psi(U, P);
+    for (int c = 0; c < NV; ++c) qv[0] -= dt * lH[c] * P[c];
+    qv[1] = d1 + d2;
+  }
+  for (int c = 0; c < 6; ++c) ab.pq[kind][id + c * n] = qv[c];
+  ab.pm[kind][id] = pm;
+}
+
+// What the lines of one direction pass to one DoF: the adjoint of its flux,
+// of the DoF itself (through alpha w and div B) and of its spectral radius.
+struct LineSum {
+  double lF[NV], lw[NV], lr;
+};
+// The line in direction dir centred at point id (of n) of a kind, in which
+// the DoF is slot m.
+AF_HD void line_use(const AdjBuf& ab, int kind, size_t id, size_t n, int dir, int m, double h, double dt, LineSum& s) {
+  const double cp[5] = {0.5, -2.0, 0.0, 2.0, -0.5}, cd[5] = {0.5, -2.0, 3.0, -2.0, 0.5};
+  const double sp = -dt * cp[m] / By(h), sd = -dt * cd[m] / By(h) * ab.pq[kind][id + (dir ? 4 : 2) * n];
+  for (int c = 0; c < NV; ++c) {
+    const double lH = ab.pH[kind][id + c * n];
+    s.lF[c] += sp * lH;
+    s.lw[c] += sd * lH;
+  }
+  s.lw[4 + dir] += cp[m] * ab.pq[kind][id] / By(h);
+  if ((int)((ab.pm[kind][id] >> (dir ? 3 : 0)) & 7u) == m + 1) s.lr += ab.pq[kind][id + (dir ? 5 : 3) * n];
+}
+// The central difference in direction dir at point id, of which the DoF is
+// the low (sgn -1) or the high (+1) state.
+AF_HD void pair_use(const AdjBuf& ab, int kind, size_t id, size_t n, int dir, double sg, double h, double dt,
+                    LineSum& s) {
+  const double sp = -dt * sg / By(h);
+  for (int c = 0; c < NV; ++c) s.lF[c] += sp * ab.pH[kind][id + c * n];
+  s.lw[4 + dir] += sg * ab.pq[kind][id] / By(h);
+}
+// The lines in direction dir that hold the DoF at index q of n cells, centred
+// at points of a kind whose index along dir is a node: full, the DoF is of
+// that kind too (slots 0, 2, 4), else half a cell on (slots 1, 3).  base and
+// stride: the index of the point at node p is base + p stride.  Across an
+// outflow boundary a line's outer states are mirrored ones, which gives the
+// DoFs next to it one use more.
+AF_HD void line_uses(const AdjBuf& ab, int kind, size_t base, size_t stride, size_t np, int dir, bool full, int q, int n,
+                     int bc, double h, double dt, LineSum& s) {
+  const int lo = q > 0 ? q - 1 : n - 1, hi = q + 1 < n + (bc ? 1 : 0) ? q + 1 : 0;
+  auto use = [&](int p, int m) { line_use(ab, kind, base + (size_t)p * stride, np, dir, m, h, dt, s); };
+  if (full) {
+    if (!bc || q > 0) use(lo, 4);
+    use(q, 2);
+    if (!bc || q < n) use(hi, 0);
+    if (bc && q == 1) use(0, 0);
+    if (bc && q == n - 1) use(n, 4);
+  } else {
+    use(q, 3);
+    use(hi, 1);
+    if (bc && q == 0) use(0, 1);
+    if (bc && q == n - 1) use(n, 3);
+  }
+}
+AF_HD void line_finish(const double* w, double gm, int dir, LineSum& s, double* lw) {
+  for (int c = 0; c < NV; ++c) lw[c] += s.lw[c];
+  flux_vjp(w, gm, dir, s.lF, lw);
+  if (s.lr != 0.0) srad_vjp(w, gm, dir, s.lr, lw);
+}
+AF_HD void line_zero(LineSum& s) {
+  zero8(s.lF);
+  zero8(s.lw);
+  s.lr = 0.0;
+}
+
+// One DoF of kind 0 X, 1 Y, 2 V or 3 centre: everything that the points'
+// lines and its own Psi pass to it, added to lam_k (for a centre: to lC).
+template <class Add>
+AF_HD void adj_lines_gather(const AGeo& g, const StateC& u, const Tape& t, const AdjBuf& ab, const StateM& lk, int kind,
+                            int k, int l, double dt) {
+  const size_t nX = point_n(g, 0), nY = point_n(g, 1), nV = point_n(g, 2);
+  const size_t id = kind == 3 ? (size_t)l * g.nx + k : point_id(g, kind, k, l);
+  const size_t n = kind == 3 ? (size_t)g.nx * g.ny : point_n(g, kind);
+  double w[NV], lw[NV];
+  ld(kind == 0 ? u.x : kind == 1 ? u.y : kind == 2 ? u.v : t.C, Loc{id, n}, w);
+  zero8(lw);
+  LineSum s;
+  // x lines
+  line_zero(s);
+  if (kind == 0)
+    line_uses(ab, 0, (size_t)l * g.nxp, 1, nX, 0, true, k, g.nx, g.bcx, g.dx, dt, s);
+  else if (kind == 3)
+    line_uses(ab, 0, (size_t)l * g.nxp, 1, nX, 0, false, k, g.nx, g.bcx, g.dx, dt, s);
+  else {
+    line_uses(ab, 2, (size_t)l * g.nxp, 1, nV, 0, kind == 2, k, g.nx, g.bcx, g.dx, dt, s);
+    if (kind == 2) {
+      if (k < g.nx) pair_use(ab, 1, (size_t)l * g.nx + k, nY, 0, -1.0, g.dx, dt, s);
+      if (k > 0 || !g.bcx) pair_use(ab, 1, (size_t)l * g.nx + (k > 0 ? k - 1 : g.nx - 1), nY, 0, 1.0, g.dx, dt, s);
+    }
+  }
+  line_finish(w, g.gamma, 0, s, lw);
+  // y lines
+  line_zero(s);
+  if (kind == 1)
+    line_uses(ab, 1, (size_t)k, (size_t)g.nx, nY, 1, true, l, g.ny, g.bcy, g.dy, dt, s);
+  else if (kind == 3)
+    line_uses(ab, 1, (size_t)k, (size_t)g.nx, nY, 1, false, l, g.ny, g.bcy, g.dy, dt, s);
+  else {
+    line_uses(ab, 2, (size_t)k, (size_t)g.nxp, nV, 1, kind == 2, l, g.ny, g.bcy, g.dy, dt, s);
+    if (kind == 2) {
+      if (l < g.ny) pair_use(ab, 0, (size_t)l * g.nxp + k, nX, 1, -1.0, g.dy, dt, s);
+      if (l > 0 || !g.bcy) pair_use(ab, 0, (size_t)(l > 0 ? l - 1 : g.ny - 1) * g.nxp + k, nX, 1, 1.0, g.dy, dt, s);
+    }
+  }
+  line_finish(w, g.gamma, 1, s, lw);
+  if (kind < 3) {  // the point itself: H = U - dt div B Psi(U) + ...
+    double lP[NV];
+    const double f = -dt * ab.pq[kind][id + n];
+    for (int c = 0; c < NV; ++c) {
+      const double lH = ab.pH[kind][id + c * n];
+      lw[c] += lH;
+      lP[c] = f * lH;
+    }
+    psi_vjp(w, lP, lw);
+  }
+  put<Add>(kind == 0 ? lk.x : kind == 1 ? lk.y : kind == 2 ? lk.v : ab.lC, Loc{id, n}, lw);
 }
 
 // Centre of real cell (i, j), first pass: the adjoint of the limited
