@@ -603,16 +603,11 @@ AF_HD void point_limit_vjp(const double* UH, const double* UL, double g, uint32_
     pres_vjp(Us, g, -ldn, lUs);
   }
   for (int c = 1; c < NV; ++c) lUH[c] += lUs[c];
-  lUH[0] += th1 * lUs[0];
-  lrhoL += (1.0 - th1) * lUs[0];
-  const double lth1 = lUs[0] * (UH[0] - rhoL);
-  if (fl & BL_T1) {
-    const double den = rhoL - UH[0];
-    const double ln = lth1 / By(den), ldn = -lth1 * th1 / By(den);
-    lrhoL += ln + ldn;
-    ler -= ln;
-    lUH[0] -= ldn;
-  }
+  // the limited density is eps_rho, whatever UH[0] and rhoL are
+  if (fl & BL_T1)
+    ler += lUs[0];
+  else
+    lUH[0] += lUs[0];
   if (fl & BL_ER) lrhoL += ler;
   if (fl & BL_EP) lpL += lep;
   lUL[0] += lrhoL;
@@ -683,12 +678,19 @@ AF_HD void centre_limit_vjp(const double* A, const double* Uc, double g, uint32_
     pres_vjp(Ur, g, -ldn, lUr);
   }
   double lth1 = 0.0;
-  for (int c = 0; c < NV; ++c) {
+  for (int c = 1; c < NV; ++c) {
     lUc[c] += th1 * lUr[c];
     lA[c] += (1.0 - th1) * lUr[c];
     lth1 += lUr[c] * (Uc[c] - A[c]);
   }
-  if (fl & BL_T1) {
+  // The limited density is eps_rho, whatever Uc[0] and rhoA are: its adjoint
+  // reaches eps_rho alone.  By way of th1 it would cancel to rounding, and it is
+  // no small number: the pressure at a density of 1e-13 makes it 1e6 where the
+  // gradient is of size 1, whose rounding is then 1e-9.
+  if (!(fl & BL_T1)) {
+    lUc[0] += lUr[0];
+  } else {
+    ler += lUr[0];
     const double den = rhoA - Uc[0];
     const double ln = lth1 / By(den), ldn = -lth1 * th1 / By(den);
     lrhoA += ln + ldn;
