@@ -164,125 +164,21 @@ __device__ __forceinline__ double cell_H(const CellsLDS64<CBX, CBY>& L, int tx, 
   }
 }
 
-// The density box of step (2) of the flux limiter into Lam, and whether the
-// sufficient test shows that no vertex of it needs the pressure shrink (the
-// operations of limiter_box).
-template <int CBX, int CBY>
-__device__ __forceinline__ bool box_clear(const CellsLDS64<CBX, CBY>& L, const double A1[NV], int tx, int ty,
-                                          double lx, double ly, double gm1, double er, double ep, double Lam[4]) {
-#pragma clang fp contract(off)
-  double h0[4], neg = 0.0;
-#pragma unroll
-  for (int I = 0; I < 4; ++I) {
-    h0[I] = cell_H(L, tx, ty, lx, ly, I, 0);
-    neg += h0[I] < 0.0 ? h0[I] : 0.0;
-  }
-#pragma unroll
-  for (int I = 0; I < 4; ++I) Lam[I] = 1.0;
-  if (A1[0] - er < LAMBDA_REG - neg) {  // else every fraction is at least 1
-#pragma unroll
-    for (int I = 0; I < 4; ++I)
-      if (h0[I] < 0.0) Lam[I] = fmin(1.0, (A1[0] - er) / (LAMBDA_REG - neg));
-  }
-  bool ok = A1[0] >= er && A1[0] > 0.0 && p_at_least(A1, ep, gm1);
-#pragma unroll
-  for (int I = 0; I < 4; ++I) {
-    double W[NV];
-#pragma unroll
-    for (int c = 0; c < NV; ++c) W[c] = A1[c] + 4.0 * (Lam[I] * cell_H(L, tx, ty, lx, ly, I, c));
-    ok = ok && W[0] >= er && W[0] > 0.0 && p_at_least(W, ep, gm1);
-  }
-  return ok;
-}
-
-// Step (2) of the flux limiter for the listed cells: sixteen lanes a cell, lane
-// k tests vertex k of the box and finds its root, the smallest root of each
-// interface's vertices by lane exchange, then the round-off fallback on the
-// final box.  Arithmetic, order within a vertex and counters are limiter_box's
-// (its loop over the vertices costs a wave 15 tests and as many root solves
-// one after the other: 28 us of a 44 us launch with 130 roots).
+// Step (2) of the flux limiter for the listed cells, sixteen lanes a cell
+// (limiter_box_lanes).
 template <int CBX, int CBY>
 __device__ __forceinline__ void box_listed(CellsLDS64<CBX, CBY>& L, const Geo& g, int i0, int j0, double lx,
                                            double ly, Counters* cn, int tid) {
-#pragma clang fp contract(off)
-  const int n = L.n, k = tid & 15;
+  const int n = L.n;
   for (int m = tid / 16; m < n; m += CBX * CBY / 16) {
     const int tx = L.l.q[m] % CBX, ty = L.l.q[m] / CBX;
-    const bool counted = cell_output<CBX, CBY>(g, i0, j0, tx, ty);
-    double A1[NV], Lr[4];
+    double A1[NV], lam[4];
 #pragma unroll
     for (int c = 0; c < NV; ++c) A1[c] = L.a1[c][m];
-    const double er = L.l.eps[0][m], ep = L.l.eps[1][m];
-    auto vertex = [&](const double B[4], double D[NV]) {
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        double d = 0.0;
-#pragma unroll
-        for (int I = 0; I < 4; ++I)
-          if (k & (1 << I)) d += B[I] * cell_H(L, tx, ty, lx, ly, I, c);
-        D[c] = d;
-      }
-    };
-    {
-      double h0[4], neg = 0.0;
-#pragma unroll
-      for (int I = 0; I < 4; ++I) {
-        h0[I] = cell_H(L, tx, ty, lx, ly, I, 0);
-        neg += h0[I] < 0.0 ? h0[I] : 0.0;
-      }
-#pragma unroll
-      for (int I = 0; I < 4; ++I) Lr[I] = h0[I] < 0.0 ? fmin(1.0, (A1[0] - er) / (LAMBDA_REG - neg)) : 1.0;
-    }
-    double r = 1.0;
-    {
-      double D[NV], W[NV];
-      vertex(Lr, D);
-#pragma unroll
-      for (int c = 0; c < NV; ++c) W[c] = A1[c] + D[c];
-      if (k > 0 && pressure(W, g.gm1) < ep) {
-        int it;
-        r = vertex_root(A1, D, g.gm1, ep, it);
-        if (counted) {
-          count(&cn->n_newton);
-          count_max(&cn->newton_iters_max, (unsigned long long)it);
-        }
-      }
-    }
-    double lam[4];
-    double any = r;
-#pragma unroll
-    for (int x = 1; x < 16; x <<= 1) any = fmin(any, __shfl_xor(any, x));
-#pragma unroll
-    for (int I = 0; I < 4; ++I) {
-      double q = k & (1 << I) ? r : 1.0;
-#pragma unroll
-      for (int x = 1; x < 16; x <<= 1) q = fmin(q, __shfl_xor(q, x));
-      lam[I] = Lr[I] * q;
-    }
-    // (a root is less than 1: the shrink of a box that needed one is checked)
-    const int base = tid & 48;
-    auto box_ok = [&](const double B[4]) {
-      double D[NV];
-      vertex(B, D);
-#pragma unroll
-      for (int c = 0; c < NV; ++c) D[c] = A1[c] + D[c];
-      const unsigned long long bad = __ballot(k > 0 && !in_G(D, g.gm1));
-      return ((bad >> base) & 0xffffull) == 0;
-    };
-    if (any < 1.0 && !box_ok(lam)) {
-      if (counted && k == 0) count(&cn->n_fallback);
-      bool found = false;
-      double B[4];
-#pragma unroll 1
-      for (int e = 0; e < 10 && !found; ++e) {
-#pragma unroll
-        for (int I = 0; I < 4; ++I) B[I] = fmax(lam[I] - ldexp(SHRINK, e), 0.0);
-        found = box_ok(B);
-      }
-#pragma unroll
-      for (int I = 0; I < 4; ++I) lam[I] = found ? B[I] : 0.0;
-    }
-    if (k == 0) {
+    auto H = [&](int I, int c) -> double { return cell_H(L, tx, ty, lx, ly, I, c); };
+    limiter_box_lanes(A1, H, g.gm1, L.l.eps[0][m], L.l.eps[1][m], lam, cn, cell_output<CBX, CBY>(g, i0, j0, tx, ty),
+                      tid);
+    if ((tid & 15) == 0) {
 #pragma unroll
       for (int I = 0; I < 4; ++I) L.a1[I][m] = lam[I];
       L.l.lam[0][ty][tx] = lam[2];
@@ -402,7 +298,8 @@ __device__ __forceinline__ void cells_tile(const Geo& g, CState u, const double*
 #pragma unroll
       for (int c = 0; c < NV; ++c) G[c] -= dt * (th * S[c] + (1.0 - th) * Sl[c]);
     }
-    if (!box_clear<CBX, CBY>(L, A1, tx, ty, lx, ly, g.gm1, er, ep, Lam)) {
+    auto H = [&](int I, int c) -> double { return cell_H(L, tx, ty, lx, ly, I, c); };
+    if (!box_clear(A1, H, g.gm1, er, ep, Lam)) {
       listed = atomicAdd(&L.n, 1);
 #pragma unroll
       for (int c = 0; c < NV; ++c) L.a1[c][listed] = A1[c];

@@ -554,4 +554,121 @@ __device__ void limiter_box(const double A1[NV], HF H, double gm1, double er, do
   for (int I = 0; I < 4; ++I) Lam[I] = 0.0;
 }
 
+// The FP64 cell tile's form of step (2), in two parts: the density box with the
+// sufficient test by the cell's own lane, and the rest by sixteen lanes for the
+// cells that fail the test.  Arithmetic, decisions and counters are
+// limiter_box's.
+
+// The density box into Lam, and whether the sufficient test shows that no
+// vertex of it needs the pressure shrink.
+template <class HF>
+__device__ __forceinline__ bool box_clear(const double A1[NV], HF H, double gm1, double er, double ep,
+                                          double Lam[4]) {
+#pragma clang fp contract(off)
+  double h0[4], neg = 0.0;
+#pragma unroll
+  for (int I = 0; I < 4; ++I) {
+    h0[I] = H(I, 0);
+    neg += h0[I] < 0.0 ? h0[I] : 0.0;
+  }
+#pragma unroll
+  for (int I = 0; I < 4; ++I) Lam[I] = 1.0;
+  if (A1[0] - er < LAMBDA_REG - neg) {  // else every fraction is at least 1
+#pragma unroll
+    for (int I = 0; I < 4; ++I)
+      if (h0[I] < 0.0) Lam[I] = fmin(1.0, (A1[0] - er) / (LAMBDA_REG - neg));
+  }
+  bool ok = A1[0] >= er && A1[0] > 0.0 && p_at_least(A1, ep, gm1);
+#pragma unroll
+  for (int I = 0; I < 4; ++I) {
+    double W[NV];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) W[c] = A1[c] + 4.0 * (Lam[I] * H(I, c));
+    ok = ok && W[0] >= er && W[0] > 0.0 && p_at_least(W, ep, gm1);
+  }
+  return ok;
+}
+
+// Without the sufficient test, by sixteen lanes (tid: the thread in its
+// workgroup; a group is sixteen aligned ones): lane k tests vertex k of the box
+// and finds its root, the smallest root of each interface's vertices comes by
+// lane exchange, then the round-off fallback on the final box.  As in
+// limiter_box the final box is checked where a vertex asked for a root, whatever
+// its size: the cubic rounds differently from the pressure, so that a vertex
+// whose pressure is lost to rounding (|B| from about 10 on) can ask for one and
+// get 1.  limiter_box's loop over the vertices costs a wave 15 tests and as many
+// root solves one after the other: 28 us of a 44 us launch with 130 roots.
+template <class HF>
+__device__ __forceinline__ void limiter_box_lanes(const double A1[NV], HF H, double gm1, double er, double ep,
+                                                  double Lam[4], Counters* cn, bool counted, int tid) {
+#pragma clang fp contract(off)
+  const int k = tid & 15, base = tid & 48;
+  auto in_any_lane = [&](bool p) { return ((__ballot(p) >> base) & 0xffffull) != 0; };
+  auto vertex = [&](const double B[4], double D[NV]) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      double d = 0.0;
+#pragma unroll
+      for (int I = 0; I < 4; ++I)
+        if (k & (1 << I)) d += B[I] * H(I, c);
+      D[c] = d;
+    }
+  };
+  double Lr[4];
+  {
+    double h0[4], neg = 0.0;
+#pragma unroll
+    for (int I = 0; I < 4; ++I) {
+      h0[I] = H(I, 0);
+      neg += h0[I] < 0.0 ? h0[I] : 0.0;
+    }
+#pragma unroll
+    for (int I = 0; I < 4; ++I) Lr[I] = h0[I] < 0.0 ? fmin(1.0, (A1[0] - er) / (LAMBDA_REG - neg)) : 1.0;
+  }
+  double r = 1.0;
+  bool asked;
+  {
+    double D[NV], W[NV];
+    vertex(Lr, D);
+#pragma unroll
+    for (int c = 0; c < NV; ++c) W[c] = A1[c] + D[c];
+    asked = k > 0 && pressure(W, gm1) < ep;
+    if (asked) {
+      int it;
+      r = vertex_root(A1, D, gm1, ep, it);
+      if (counted) {
+        count(&cn->n_newton);
+        count_max(&cn->newton_iters_max, (unsigned long long)it);
+      }
+    }
+  }
+#pragma unroll
+  for (int I = 0; I < 4; ++I) {
+    double q = k & (1 << I) ? r : 1.0;
+#pragma unroll
+    for (int x = 1; x < 16; x <<= 1) q = fmin(q, __shfl_xor(q, x));
+    Lam[I] = Lr[I] * q;
+  }
+  auto box_ok = [&](const double B[4]) {
+    double D[NV];
+    vertex(B, D);
+#pragma unroll
+    for (int c = 0; c < NV; ++c) D[c] = A1[c] + D[c];
+    return !in_any_lane(k > 0 && !in_G(D, gm1));
+  };
+  if (in_any_lane(asked) && !box_ok(Lam)) {
+    if (counted && k == 0) count(&cn->n_fallback);
+    bool found = false;
+    double B[4];
+#pragma unroll 1
+    for (int e = 0; e < 10 && !found; ++e) {
+#pragma unroll
+      for (int I = 0; I < 4; ++I) B[I] = fmax(Lam[I] - ldexp(SHRINK, e), 0.0);
+      found = box_ok(B);
+    }
+#pragma unroll
+    for (int I = 0; I < 4; ++I) Lam[I] = found ? B[I] : 0.0;
+  }
+}
+
 }  // namespace afm
