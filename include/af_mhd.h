@@ -189,8 +189,9 @@ void af_mhd_destroy(af_mhd_ctx* c);
 int af_mhd_stream_copy(const double* src, double* dst, size_t n, void* hip_stream);
 
 /* ------------------------------------------------------------ limiters
- * The stage's positivity limiters applied to n given inputs, one device
- * thread per item, with the same device code the stage kernels run:
+ * The stage's positivity limiters applied to n given inputs with the same
+ * device code the stage kernels run (one device thread per item; AF_LIM_BOX
+ * sixteen, as in the FP64 stage):
  *   AF_LIM_POINT   scaling limiter of a point value (Section 3.3):
  *                  in [n][16] = (U^H, U^LLF), out [n][8] = limited value
  *   AF_LIM_CENTRE  limiter of the centre value towards the cell average
@@ -202,7 +203,9 @@ int af_mhd_stream_copy(const double* src, double* dst, size_t n, void* hip_strea
  *                  A^src = G - dt S^s; out [n][9] = (A^{Lim,1}, theta_src)
  *   AF_LIM_BOX     step (2): density box and the pressure shrink over the 15
  *                  non-trivial vertices; in [n][42] = (A^{Lim,1}, H_L, H_R,
- *                  H_D, H_U, eps_rho, eps_p), out [n][4] = Lambda_{L,R,D,U}
+ *                  H_D, H_U, eps_rho, eps_p), out [n][4] = Lambda_{L,R,D,U},
+ *                  NaN if the FP64 and the FP32-bulk stage's forms of this
+ *                  step differ in a bit
  * Each applies the round-off fallback of the closing remark of Section 4
  * (coefficient shrunk by 2^m 1e-8, m = 0..9, each trial from the original
  * value, floored at 0, when the limited state falls outside G).  Limiter
