@@ -40,11 +40,13 @@ __device__ __forceinline__ void acc_zero(PointAcc& P) {
 // when also p(U) >= 2e-12, rho(U) >= 2e-12 and E of the stencil <= 5e11 p(U)
 // (0.1 p(U) is then far above the 1e-16 E that rounding leaves in p(U^LLF)),
 // the LLF state is known to pass its test, and neither it nor its fluxes are
-// formed.  Every other point takes the general path: the LLF state from its
-// four neighbours, then the limiter.  The bound costs a line about 30
-// instructions where its two LLF fluxes cost 130 (3497 -> 2552 VALU
-// instructions per thread of the tile); at CFL 0.2 smooth flow stays near 0.4.
-// Above CFL 0.45 the fastest points of a grid begin to fail it.
+// formed.  Every other point is listed: a point whose high-order state is not
+// admissible for its limiter, any other for the count of LLF states outside G,
+// the only thing that its LLF state decides (both of the limiter's bounds are at
+// most 1e-13).  The bound costs a line about 30 instructions where its two LLF
+// fluxes cost 130 (3497 -> 2552 VALU instructions per thread of the tile); at CFL
+// 0.2 smooth flow stays near 0.4, above CFL 0.45 most points of a grid can fail
+// it.
 constexpr double LLF_BOUND = 0.9, LLF_MIN = 2e-12, LLF_EMAX = 5e11;
 
 // One direction's term for a point: vc, llf_speeds of the three states; jump,
@@ -84,20 +86,38 @@ __device__ __forceinline__ constexpr int point_exchange(int c) {  // ten fields
   return c < 5 ? QV_ + c : c == 5 ? QX_ + 3 : c == 6 ? QY_ + 3 : 30 + c;
 }
 
-// The points whose limiter may act: kind << 8 | ty << 4 | tx (kind 0 V, 1 X,
-// 2 Y); at most three for each of the (PB-2)^2 cells.
-struct LimitList {
-  int n;
-  unsigned short q[3 * (PB - 2) * (PB - 2)];
+// The listed points: kind << 8 | ty << 4 | tx (kind 0 V, 1 X, 2 Y), at most three
+// for each of the (PB-2)^2 cells.  From the front those whose limiter acts, from
+// the back those whose LLF state is only looked at.
+constexpr int LOOK_END = 3 * (PB - 2) * (PB - 2);
+struct PointList {
+  int limit, look;
+  unsigned short q[LOOK_END];
 };
-constexpr int LIST_ = 37;
-static_assert(sizeof(LimitList) <= (POINT_FIELDS - LIST_) * PB * PB * sizeof(double), "list in the spare fields");
-__device__ __forceinline__ LimitList& limit_list(double (*s)[PB][PB]) {
-  return *reinterpret_cast<LimitList*>(&s[LIST_][0][0]);
+constexpr int LIST_ = 37, QXY_ = 38, QYX_ = 39;  // QXY_, QYX_: c_f of X in y, of Y in x (look_listed)
+static_assert(sizeof(PointList) <= PB * PB * sizeof(double), "list in a spare field");
+__device__ __forceinline__ PointList& point_list(double (*s)[PB][PB]) {
+  return *reinterpret_cast<PointList*>(&s[LIST_][0][0]);
 }
-__device__ __forceinline__ void limit_later(double (*s)[PB][PB], int kind, int ty, int tx) {
-  LimitList& L = limit_list(s);
-  L.q[atomicAdd(&L.n, 1)] = (unsigned short)(kind << 8 | ty << 4 | tx);
+struct PointEnd {  // what a finished point still needs
+  bool limit, look;
+};
+// Called by whole wavefronts: one LDS atomic each and list.
+__device__ __forceinline__ void list_point(double (*s)[PB][PB], PointEnd end, int kind, int ty, int tx) {
+  if (__builtin_expect(!__ballot(end.limit | end.look), 1)) return;
+  PointList& L = point_list(s);
+  const unsigned long long lim = __ballot(end.limit), look = __ballot(end.look);
+  const int lane = __lane_id();
+  int a = 0, b = 0;
+  if (lane == 0) {
+    if (lim) a = atomicAdd(&L.limit, __popcll(lim));
+    if (look) b = atomicAdd(&L.look, __popcll(look));
+  }
+  a = __builtin_amdgcn_readfirstlane(a);
+  b = __builtin_amdgcn_readfirstlane(b);
+  const unsigned long long below = (1ull << lane) - 1;
+  const int at = end.limit ? a + __popcll(lim & below) : LOOK_END - 1 - b - __popcll(look & below);
+  if (end.limit | end.look) L.q[at] = (unsigned short)(kind << 8 | ty << 4 | tx);
 }
 
 // --------------------------------------------------- point tile
@@ -252,31 +272,50 @@ __device__ __forceinline__ void add_line(PointAcc& P, const double Q[NV], double
 }
 
 // The high-order state of a finished point from its accumulators, and, where
-// the limiter returns it unchanged (see llf_bound), SSP combination and store.
-// Elsewhere it goes to the same place of `stash` and true is returned: the
-// point is to be listed.  un: the point's set of U^n (read only when ca != 0).
-__device__ __forceinline__ bool finish(const Geo& g, double dt, const double U0[NV], const PointAcc& P, double ca,
-                                       double cb, const double* un, double* out, double* stash, long plane, long off,
-                                       bool speeds, double& wm) {
+// the limiter returns it unchanged, SSP combination and store: where the bound
+// shows it (see llf_bound), and where the state satisfies rho, p >= 1e-13 whatever
+// the LLF state is (to be looked at: that one is still to be counted).  Elsewhere
+// it goes to the same place of `stash` (to be limited).  un: the point's set of
+// U^n (read only when ca != 0).
+__device__ __forceinline__ PointEnd finish(const Geo& g, double dt, const double U0[NV], const PointAcc& P, double ca,
+                                           double cb, const double* un, double* out, double* stash, long plane,
+                                           long off, bool speeds, double& wm) {
   double UH[NV], Un[NV], Ps[NV];
   if (ca != 0.0) load8(un, plane, off, Un);  // in flight over the tests
   psi(U0, Ps);
 #pragma unroll
   for (int c = 0; c < NV; ++c) UH[c] = U0[c] + dt * (P.h[c] - P.divh * Ps[c]);
-  if (!((P.bnd <= LLF_BOUND) & (UH[0] >= EPS_FLOOR) & p_at_least(UH, EPS_FLOOR, g.gm1))) {
+  auto put = [&](double W[NV]) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) out[c * plane + off] = W[c];
+    // a step's last stage: the next step's wave-speed maximum over its outputs
+    if (speeds) wm = fmax(wm, dt_speed(W, g));
+  };
+  auto store = [&]() {  // with the SSP combination
+    if (ca != 0.0) {
+#pragma unroll
+      for (int c = 0; c < NV; ++c) Un[c] = ca * Un[c] + cb * UH[c];
+      put(Un);
+      asm volatile("");  // the stores stay in the branch: joined, they cost 16 moves
+    } else {
+      put(UH);
+    }
+  };
+  if (__builtin_expect(!((P.bnd <= LLF_BOUND) & (UH[0] >= EPS_FLOOR) & p_at_least(UH, EPS_FLOOR, g.gm1)), 0)) {
+    // the limiter would look at the state again: by more than what its form of
+    // the pressure can round (behind the empty asm, or it is formed for all)
+    double E = UH[7];
+    asm volatile("" : "+v"(E));
+    if ((UH[0] >= EPS_FLOOR) & p_at_least(UH, fma(1e-14 * g.gm1, E, EPS_FLOOR), g.gm1)) {
+      store();
+      return PointEnd{false, true};
+    }
 #pragma unroll
     for (int c = 0; c < NV; ++c) stash[c * plane + off] = UH[c];
-    return true;
+    return PointEnd{true, false};
   }
-  if (ca != 0.0) {
-#pragma unroll
-    for (int c = 0; c < NV; ++c) UH[c] = ca * Un[c] + cb * UH[c];
-  }
-#pragma unroll
-  for (int c = 0; c < NV; ++c) out[c * plane + off] = UH[c];
-  // a step's last stage: the next step's wave-speed maximum over its outputs
-  if (speeds) wm = fmax(wm, dt_speed(UH, g));
-  return false;
+  store();
+  return PointEnd{false, false};
 }
 
 // The value of a kind (0 V, 1 X, 2 Y) out of three uniform ones.  The empty
@@ -298,11 +337,11 @@ __device__ __forceinline__ void load_point(const Geo& g, CState u, int kind, int
         (long)jj * of_kind(kind, g.nxp, g.nxp, g.nx) + ii, U);
 }
 
-// The tile's listed points, their high-order states in `stash`: the
+// The tile's nl points to be limited, their high-order states in `stash`: the
 // first-order LLF state (Section 3.3), the scaling limiter, SSP combination,
-// store.  V and the FVS direction of X and Y take the own type's neighbours
-// at +-h, the central direction of X and Y the two vertices; the point's own
-// flux cancels between the two pairs of a direction,
+// store; and the LLF states of the first n - nl points to be looked at.  V and the FVS direction of X and Y take the own type's neighbours at
+// +-h, the central direction of X and Y the two vertices; the point's own flux
+// cancels between the two pairs of a direction,
 //   U^LLF = U - sum (dt/Delta) [(F+ - F-) - al+ (U+ - U) + al- (U - U-)] / 2 - dt div B Psi.
 // Four lanes share a point, a neighbour each, and every wave of the tile
 // takes its part of the list: a shock's points lie in few tiles, whose time
@@ -310,18 +349,18 @@ __device__ __forceinline__ void load_point(const Geo& g, CState u, int kind, int
 // 37 us launch (200 x 137 grid with 300 such points).
 __device__ __forceinline__ void limit_listed(double (*s)[PB][PB], const Geo& g, CState u, CState un, MState out,
                                              MState stash, double dt, double ca, double cb, Counters* cn, int bx,
-                                             int by, int tid, bool speeds, double& wm) {
-  const LimitList& L = limit_list(s);
-  const int n = L.n;
+                                             int by, int tid, int nl, int n, bool speeds, double& wm) {
+  const PointList& L = point_list(s);
   for (int k = tid / 4; k < n; k += PNT / 4) {
-    const int e = L.q[k], kind = e >> 8, m = tid & 3, dir = m >> 1;
+    const bool act = k < nl;
+    const int e = L.q[act ? k : LOOK_END - 1 - (k - nl)], kind = e >> 8, m = tid & 3, dir = m >> 1;
     const int i = bx * (PB - 2) - 1 + (e & 15), j = by * (PB - 2) - 1 + (e >> 4 & 15);
     const bool hi = m & 1, own = kind == 0 || dir == kind - 1, lead = m == 0;
     const int d = hi ? 1 : (own ? -1 : 0);
     const long plane = of_kind(kind, g.sv, g.sx, g.sy), off = (long)j * of_kind(kind, g.nxp, g.nxp, g.nx) + i;
     double U0[NV], UH[NV], l[NV], divl;
     load_point(g, u, kind, i, j, U0);
-    load8(of_kind(kind, stash.v, stash.x, stash.y), plane, off, UH);
+    if (act) load8(of_kind(kind, stash.v, stash.x, stash.y), plane, off, UH);
     {
       double W[NV];
       DirEval e0, e1;
@@ -345,6 +384,7 @@ __device__ __forceinline__ void limit_listed(double (*s)[PB][PB], const Geo& g, 
 #pragma unroll
     for (int c = 0; c < NV; ++c) l[c] = U0[c] + (l[c] - dt * divl * W[c]);
     if (lead && !in_G_fast(l)) count(&cn->n_llf_not_admissible);
+    if (!act) continue;
     limit_point(UH, l, g.gm1, W, cn, lead);
     if (!lead) continue;
     if (!in_G_fast(W)) count(&cn->n_not_admissible);
@@ -357,6 +397,62 @@ __device__ __forceinline__ void limit_listed(double (*s)[PB][PB], const Geo& g, 
 #pragma unroll
     for (int c = 0; c < NV; ++c) o[c * plane + off] = W[c];
     if (speeds) wm = fmax(wm, dt_speed(W, g));
+  }
+}
+
+// More points to be looked at than what limit_listed does in one round, and they
+// take look_listed.
+constexpr int LOOK_MIN = PNT / 4;
+// Their LLF states, a lane each, from the tile's states and records in LDS (the
+// vertices and the records in the other direction are put back first).  Four
+// lanes each with their states from memory take too long where most points of a
+// tile fail the bound: Orszag-Tang vortex 512^2 at CFL 0.5, 457 us a step with
+// limit_listed alone, 323 with this (without any bound, every LLF flux formed
+// beside its line: 329).  What bounds it is VALU issue, 380 instructions a point.
+__device__ __forceinline__ void look_listed(double (*s)[PB][PB], const Geo& g, double lxr, double lyr, double dt,
+                                            Counters* cn, int tid, int n) {
+  const PointList& L = point_list(s);
+  for (int k = tid; k < n; k += PNT) {
+    const int e = L.q[LOOK_END - 1 - k], kind = e >> 8, ty = e >> 4 & 15, tx = e & 15;
+    const int so = 8 * kind, qo = kind == 0 ? QV_ : kind == 1 ? QX_ : QY_;
+    double U0[NV], l[NV], div = 0.0, w0 = 1.0;  // l: without the point's own part w0 U0
+    lds8(s, so, ty, tx, U0);
+    const double r0 = s[qo][ty][tx], sq0 = s[qo + 2][ty][tx];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) l[c] = 0.0;
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+      // c_f fields of the point and of its neighbours, which are vertices in
+      // the central direction
+      const bool own = kind == 0 || dir == kind - 1;
+      const int f0 = kind == 0 ? QV_ + 3 + dir : kind == 1 ? (dir ? QXY_ : QX_ + 3) : (dir ? QY_ + 3 : QYX_);
+      const int sn = own ? so : SV_, qn = own ? qo : QV_, fn = own ? f0 : QV_ + 3 + dir;
+      const double c0 = s[f0][ty][tx], v0 = U0[1 + dir] * r0, lam = 0.5 * (dir ? lyr : lxr);
+#pragma unroll 1
+      for (int hi = 0; hi < 2; ++hi) {
+        const int d = hi ? 1 : (own ? -1 : 0), yy = dir ? ty + d : ty, xx = dir ? tx : tx + d;
+        double F[NV], W[NV];
+        lean_pt(s, sn, qn, yy, xx, dir, F, W);
+        const double cw = s[fn][yy][xx], vw = W[1 + dir] * s[qn][yy][xx], t = sq0 + s[qn + 2][yy][xx];
+        // alpha_llf: |Roe average| lies between |v0| and |vw|; the jump by one
+        // reciprocal root of (t |jump B|)^2
+        const double j2 = jump2(U0, W), x = fmax(j2 * t * t, 1e-290);
+        double r = __builtin_amdgcn_rsq(x);
+        r = r * fma(-0.5 * x * r, r, 1.5);
+        double al = fmax(fabs(v0), fabs(vw)) + fmax(c0, cw) + j2 * r;
+        al *= lam;
+        const double sg = hi ? -lam : lam;
+#pragma unroll
+        for (int c = 0; c < NV; ++c) l[c] = fma(al, W[c], fma(sg, F[c], l[c]));
+        w0 -= al;
+        div -= sg * W[4 + dir];
+      }
+    }
+    double Ps[NV];
+    psi(U0, Ps);
+#pragma unroll
+    for (int c = 0; c < NV; ++c) l[c] = fma(w0, U0[c], fma(-div, Ps[c], l[c]));
+    if (!in_G_fast(l)) count(&cn->n_llf_not_admissible);
   }
 }
 
@@ -589,7 +685,7 @@ __device__ __forceinline__ void points_tile(const Geo& g, CState u, CState un, M
   double wm = 0.0;
   const bool speeds = wslot != nullptr;
   const double rdx = g.rdx, rdy = g.rdy, lxr = dt * g.rdx, lyr = dt * g.rdy;
-  bool later = false;  // the thread's vertex is to be listed
+  PointEnd end{false, false};  // the thread's vertex
 
   // the tile's point values into LDS, with the records of lines b and a
   {
@@ -665,13 +761,13 @@ __device__ __forceinline__ void points_tile(const Geo& g, CState u, CState un, M
       add_line(PV, Q, dB, bnd, 0.5 * rdx);
       double w[NV];
       lds8(s, SV_, t.ty, t.tx, w);
-      later = finish(g, dt, w, PV, ca, cb, un.v, out.v, stash.v, g.sv, (long)t.j * g.nxp + t.i, speeds, wm);
+      end = finish(g, dt, w, PV, ca, cb, un.v, out.v, stash.v, g.sv, (long)t.j * g.nxp + t.i, speeds, wm);
     }
   }
   pin_acc(P2);
   __syncthreads();
   // the centre values take the vertices' place; records of lines c and d
-  if (tid == 0) limit_list(s).n = 0;
+  if (tid == 0) point_list(s).limit = point_list(s).look = 0;
   {
     const PtPlace t = pt_place(g, bx, by, tid);
     if (t.grp == 0) {
@@ -710,23 +806,46 @@ __device__ __forceinline__ void points_tile(const Geo& g, CState u, CState un, M
   {
     const PtPlace t = pt_place(g, bx, by, tid);
     double w[NV];
-    if (later) limit_later(s, 0, t.ty, t.tx);
+    if (t.grp == 1) list_point(s, end, 0, t.ty, t.tx);
+    end = PointEnd{false, false};
     if (t.grp == 0) {
       if (t.outX) {
         add_line(P2, Q, dB, bnd, 0.5 * rdx);
         lds8(s, SX_, t.ty, t.tx, w);
-        if (finish(g, dt, w, P2, ca, cb, un.x, out.x, stash.x, g.sx, (long)t.j * g.nxp + t.i, speeds, wm))
-          limit_later(s, 1, t.ty, t.tx);
+        end = finish(g, dt, w, P2, ca, cb, un.x, out.x, stash.x, g.sx, (long)t.j * g.nxp + t.i, speeds, wm);
       }
     } else if (t.outY) {
       add_line(P2, Q, dB, bnd, 0.5 * rdy);
       lds8(s, SY_, t.ty, t.tx, w);
-      if (finish(g, dt, w, P2, ca, cb, un.y, out.y, stash.y, g.sy, (long)t.j * g.nx + t.i, speeds, wm))
-        limit_later(s, 2, t.ty, t.tx);
+      end = finish(g, dt, w, P2, ca, cb, un.y, out.y, stash.y, g.sy, (long)t.j * g.nx + t.i, speeds, wm);
     }
+    list_point(s, end, 1 + t.grp, t.ty, t.tx);
   }
   __syncthreads();
-  limit_listed(s, g, u, un, out, stash, dt, ca, cb, cn, bx, by, tid, speeds, wm);
+  const int nl = point_list(s).limit, nk = point_list(s).look;
+  if (__builtin_expect(nl | nk, 0))
+    limit_listed(s, g, u, un, out, stash, dt, ca, cb, cn, bx, by, tid, nl, nk > LOOK_MIN ? nl : nl + nk, speeds, wm);
+  if (__builtin_expect(nk > LOOK_MIN, 0)) {
+    const PtPlace t = pt_place(g, bx, by, tid);
+    double w[NV];
+    if (t.grp == 0) {
+      ldV(g, u.v, t.i, t.j, w);
+      sts8(s, SV_, t.ty, t.tx, w);
+      put_record(s, g, QV_, t.ty, t.tx, w, true, 0);
+      s[QV_ + 2][t.ty][t.tx] = sqrt_r(w[0]);
+    } else {
+      lds8(s, SX_, t.ty, t.tx, w);
+      double b2 = w[4] * w[4] + w[5] * w[5] + w[6] * w[6];
+      s[QXY_][t.ty][t.tx] = fast_speed(w, g.gamma, s[QX_][t.ty][t.tx], b2, s[QX_ + 2][t.ty][t.tx], 1);
+      s[QX_ + 2][t.ty][t.tx] = sqrt_r(w[0]);
+      lds8(s, SY_, t.ty, t.tx, w);
+      b2 = w[4] * w[4] + w[5] * w[5] + w[6] * w[6];
+      s[QYX_][t.ty][t.tx] = fast_speed(w, g.gamma, s[QY_][t.ty][t.tx], b2, s[QY_ + 2][t.ty][t.tx], 0);
+      s[QY_ + 2][t.ty][t.tx] = sqrt_r(w[0]);
+    }
+    __syncthreads();
+    look_listed(s, g, lxr, lyr, dt, cn, tid, nk);
+  }
   if (wslot) {
     __syncthreads();  // the LDS is reused as the reduction's scratch
     block_max_store(wm, tid, PNT, reinterpret_cast<double*>(&s[0][0][0]), wslot);

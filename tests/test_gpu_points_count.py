@@ -1,0 +1,59 @@
+"""Points whose high-order state is admissible while the bound says nothing of
+their LLF state: that state is only counted.  Noisy data and steps beyond the CFL
+bound, so that some of them are outside G; tiles that list fewer such points than
+the four-lane pass takes (14 x 14, noise 0.1: 120) and tiles that list more.  The
+counts are the oracle's; the state within the single-stage bar of the other
+parity tests, 1e-11 of each field's largest value, or four times what the
+oracle's own stage moves by when its input is perturbed by one ulp."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from paper_2506_04857_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+REL = 1e-11
+
+
+def noisy(u, hi, gamma, seed=1):
+    """White noise around (rho, v, B, p) = (1, 0, 0.5, 1), stronger along x."""
+    rng = np.random.default_rng(seed)
+    out = []
+    for a in u:
+        amp, s = np.linspace(0.005, hi, a.shape[2]), a.shape[1:]
+        rho = np.exp(amp * rng.standard_normal(s))
+        v = amp * rng.standard_normal((3,) + s)
+        b = amp * rng.standard_normal((3,) + s) + 0.5
+        p = np.exp(amp * rng.standard_normal(s))
+        out.append(np.stack([rho, *(rho * v), *b, p / (gamma - 1) + 0.5 * rho * (v * v).sum(0) + 0.5 * (b * b).sum(0)]))
+    return tuple(out)
+
+
+def worst(got, ref):
+    return max(np.max(np.abs(g[k] - r[k])) / np.max(np.abs(r[k])) for g, r in zip(got, ref) for k in range(8))
+
+
+@pytest.mark.parametrize("nx,ny,bc,hi,factor", [(14, 14, I.PERIODIC, 0.1, 16.0), (14, 14, I.PERIODIC, 0.05, 16.0),
+                                                (43, 17, I.OUTFLOW, 0.05, 16.0), (15, 29, I.PERIODIC, 0.1, 8.0)])
+def test_counted_llf_states(oracle, nx, ny, bc, hi, factor):
+    from oracle import oracle as O
+    from paper_2506_04857_amd import af_mhd as af
+    prob = replace(I.random_smooth(nx, ny, seed=nx, bc=bc), cfl=0.9, kappa=0.0)
+    u = noisy(I.sample(prob), hi, prob.gamma)
+    dt = factor * oracle.dt(prob, u)
+    c = O.Counters()
+    ref = oracle.stage(prob, 0, u, u, dt, counters=c)
+    rng = np.random.default_rng(0)
+    up = tuple(a * (1 + rng.choice([-1.0, 1.0], size=a.shape) * 2.0 ** -52) for a in u)
+    bar = max(REL, 4 * worst(oracle.stage(prob, 0, up, up, dt), ref))
+    ctx = af.Context(prob)
+    ctx.dt_dev.fill_(dt)
+    out = af.empty_state(prob)
+    ctx.af_mhd_stage(0, af.to_device(u), af.to_device(u), out)
+    st = ctx.af_mhd_stats(out)
+    ctx.close()
+    assert c.n_llf_not_admissible > 0
+    assert worst(af.to_host(out), ref) <= bar
+    assert st["n_llf_not_admissible"] == c.n_llf_not_admissible and st["n_point_limited"] == c.n_point_limited
