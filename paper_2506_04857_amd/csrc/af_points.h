@@ -409,8 +409,8 @@ constexpr int LOOK_MIN = PNT / 4;
 // tile fail the bound: Orszag-Tang vortex 512^2 at CFL 0.5, 457 us a step with
 // limit_listed alone, 323 with this (without any bound, every LLF flux formed
 // beside its line: 329).  What bounds it is VALU issue, 380 instructions a point.
-__device__ __forceinline__ void look_listed(double (*s)[PB][PB], const Geo& g, double lxr, double lyr, double dt,
-                                            Counters* cn, int tid, int n) {
+__device__ __forceinline__ void look_listed(double (*s)[PB][PB], const Geo& g, double dt, Counters* cn, int tid,
+                                            int n) {
   const PointList& L = point_list(s);
   for (int k = tid; k < n; k += PNT) {
     const int e = L.q[LOOK_END - 1 - k], kind = e >> 8, ty = e >> 4 & 15, tx = e & 15;
@@ -427,7 +427,7 @@ __device__ __forceinline__ void look_listed(double (*s)[PB][PB], const Geo& g, d
       const bool own = kind == 0 || dir == kind - 1;
       const int f0 = kind == 0 ? QV_ + 3 + dir : kind == 1 ? (dir ? QXY_ : QX_ + 3) : (dir ? QY_ + 3 : QYX_);
       const int sn = own ? so : SV_, qn = own ? qo : QV_, fn = own ? f0 : QV_ + 3 + dir;
-      const double c0 = s[f0][ty][tx], v0 = U0[1 + dir] * r0, lam = 0.5 * (dir ? lyr : lxr);
+      const double c0 = s[f0][ty][tx], v0 = U0[1 + dir] * r0, lam = 0.5 * dt * (dir ? g.rdy : g.rdx);
 #pragma unroll 1
       for (int hi = 0; hi < 2; ++hi) {
         const int d = hi ? 1 : (own ? -1 : 0), yy = dir ? ty + d : ty, xx = dir ? tx : tx + d;
@@ -684,7 +684,9 @@ __device__ __forceinline__ void points_tile(const Geo& g, CState u, CState un, M
                                             int bx, int by, double (*s)[PB][PB], double* __restrict__ wslot, int tid) {
   double wm = 0.0;
   const bool speeds = wslot != nullptr;
-  const double rdx = g.rdx, rdy = g.rdy, lxr = dt * g.rdx, lyr = dt * g.rdy;
+  const double rdx = g.rdx, rdy = g.rdy;
+  // dt / Delta of the bound, which holds for no step backward in time
+  const double lxr = dt >= 0.0 ? dt * g.rdx : 1e300, lyr = dt >= 0.0 ? dt * g.rdy : 1e300;
   PointEnd end{false, false};  // the thread's vertex
 
   // the tile's point values into LDS, with the records of lines b and a
@@ -844,7 +846,7 @@ __device__ __forceinline__ void points_tile(const Geo& g, CState u, CState un, M
       s[QY_ + 2][t.ty][t.tx] = sqrt_r(w[0]);
     }
     __syncthreads();
-    look_listed(s, g, lxr, lyr, dt, cn, tid, nk);
+    look_listed(s, g, dt, cn, tid, nk);
   }
   if (wslot) {
     __syncthreads();  // the LDS is reused as the reduction's scratch

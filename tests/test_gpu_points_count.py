@@ -1,6 +1,6 @@
 """Points whose high-order state is admissible while the bound says nothing of
 their LLF state: that state is only counted.  Noisy data and steps beyond the CFL
-bound, so that some of them are outside G; tiles that list fewer such points than
+bound or backward in time, so that some of them are outside G; tiles that list fewer such points than
 the four-lane pass takes (14 x 14, noise 0.1: 120) and tiles that list more.  The
 counts are the oracle's; the state within the single-stage bar of the other
 parity tests, 1e-11 of each field's largest value, or four times what the
@@ -36,7 +36,8 @@ def worst(got, ref):
 
 
 @pytest.mark.parametrize("nx,ny,bc,hi,factor", [(14, 14, I.PERIODIC, 0.1, 16.0), (14, 14, I.PERIODIC, 0.05, 16.0),
-                                                (43, 17, I.OUTFLOW, 0.05, 16.0), (15, 29, I.PERIODIC, 0.1, 8.0)])
+                                                (43, 17, I.OUTFLOW, 0.05, 16.0), (15, 29, I.PERIODIC, 0.1, 8.0),
+                                                (15, 29, I.OUTFLOW, 0.1, -8.0)])
 def test_counted_llf_states(oracle, nx, ny, bc, hi, factor):
     from oracle import oracle as O
     from paper_2506_04857_amd import af_mhd as af
