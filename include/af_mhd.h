@@ -346,7 +346,9 @@ typedef struct af_mhd_adj af_mhd_adj;  /* opaque host object */
 size_t af_mhd_adj_tape_bytes(const af_mhd_params* p);
 
 /* Bytes of the adjoint context's device workspace (adjoints of the stage's
- * intermediate quantities).  0 for invalid parameters. */
+ * intermediate quantities; on grids of more than 64000 points, X, Y and V
+ * together, also what their lines hand over, 45 doubles a cell).  0 for
+ * invalid parameters. */
 size_t af_mhd_adj_workspace_bytes(const af_mhd_params* p);
 
 /* Create an adjoint context; workspace_dev: caller-owned, 256-byte

@@ -226,6 +226,7 @@ constexpr long SCATTER_POINTS = 64000;
 // 200^2 2692 / 2916, 256^2 4043 / 3621, 512^2 11096 / 9958.
 constexpr long ONE_STREAM_POINTS = 160000;
 long points_of(const AGeo& g) { return (long)g.nxp * g.ny + (long)g.nx * g.nyp + (long)g.nxp * g.nyp; }
+bool gathers(const AGeo& g) { return points_of(g) > SCATTER_POINTS; }
 
 const double RK_A[3] = {0.0, 0.75, 1.0 / 3.0};
 const double RK_B[3] = {1.0, 0.25, 2.0 / 3.0};
@@ -285,7 +286,8 @@ size_t af_mhd_adj_tape_bytes(const af_mhd_params* p) {
 
 size_t af_mhd_adj_workspace_bytes(const af_mhd_params* p) {
   if (!valid_params(p)) return 0;
-  return adjbuf_layout(make_ageo(p), nullptr, nullptr);
+  const AGeo g = make_ageo(p);
+  return adjbuf_layout(g, nullptr, nullptr, nullptr, gathers(g));
 }
 
 int af_mhd_adj_init(const af_mhd_params* p, void* workspace_dev, size_t workspace_bytes, void* hip_stream,
@@ -296,13 +298,13 @@ int af_mhd_adj_init(const af_mhd_params* p, void* workspace_dev, size_t workspac
   if (!workspace_dev || ((uintptr_t)workspace_dev & 255))
     return adj_init_err = "af_mhd_adj_init: workspace null or not 256-byte aligned", AF_EINVAL;
   const AGeo g = make_ageo(p);
-  const size_t need = adjbuf_layout(g, nullptr, nullptr);
+  const size_t need = adjbuf_layout(g, nullptr, nullptr, nullptr, gathers(g));
   if (workspace_bytes < need) return adj_init_err = "af_mhd_adj_init: workspace too small", AF_EWORKSPACE;
   af_mhd_adj* c = new (std::nothrow) af_mhd_adj();
   if (!c) return adj_init_err = "af_mhd_adj_init: out of host memory", AF_EINVAL;
   c->g = g;
   size_t zeroed = 0;
-  adjbuf_layout(g, static_cast<char*>(workspace_dev), &c->ab, &zeroed);
+  adjbuf_layout(g, static_cast<char*>(workspace_dev), &c->ab, &zeroed, gathers(g));
   c->ab_base = static_cast<double*>(workspace_dev);
   c->ab_doubles = zeroed / sizeof(double);
   c->tape_bytes = tape_layout(g, nullptr, nullptr);
@@ -374,7 +376,7 @@ int af_mhd_adj_stage(af_mhd_adj* c, int k, const af_mhd_state* uk, const void* t
   (void)hipGetLastError();
   // the points' reverse beside the cells'
   const long points = points_of(g);
-  const bool gather = points > SCATTER_POINTS;
+  const bool gather = gathers(g);
   const hipStream_t side = c->side();
   hipError_t he = hipSuccess;
   if (gather) {  // only the last of the three needs the zeroed buffers

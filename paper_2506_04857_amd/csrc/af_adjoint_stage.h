@@ -121,8 +121,9 @@ inline size_t tape_layout(const AGeo& g, char* base, Tape* t) {
   if (t) *t = x;
   return off;
 }
-// zeroed: the bytes, from the start, that a sweep begins with zeros in.
-inline size_t adjbuf_layout(const AGeo& g, char* base, AdjBuf* a, size_t* zeroed = nullptr) {
+// zeroed: the bytes, from the start, that a sweep begins with zeros in.  gather:
+// whether the points' lines are gathered, which takes another 45 doubles a cell.
+inline size_t adjbuf_layout(const AGeo& g, char* base, AdjBuf* a, size_t* zeroed = nullptr, bool gather = true) {
   const Sizes s = sizes_of(g);
   size_t off = 0;
   auto take = [&](size_t n) -> double* {
@@ -145,9 +146,10 @@ inline size_t adjbuf_layout(const AGeo& g, char* base, AdjBuf* a, size_t* zeroed
   x.lSll = take(8 * s.ne);
   if (zeroed) *zeroed = off;
   for (int q = 0; q < 3; ++q) {
-    x.pH[q] = take(8 * s.set[q + 1]);
-    x.pq[q] = take(6 * s.set[q + 1]);
-    x.pm[q] = (uint32_t*)take((s.set[q + 1] + 1) / 2);
+    const size_t n = gather ? s.set[q + 1] : 0;
+    x.pH[q] = take(8 * n);
+    x.pq[q] = take(6 * n);
+    x.pm[q] = (uint32_t*)take((n + 1) / 2);
   }
   if (a) *a = x;
   return off;
