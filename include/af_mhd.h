@@ -75,7 +75,12 @@ typedef struct {
 
 /* Record HIP events on the context's stream around every kernel launch so
  * that af_mhd_kernel_times can report per-kernel device time.  Costs one
- * event record per launch boundary; off by default. */
+ * event record per launch boundary; off by default.  A timed FP64 context
+ * launches the point and the cell update apart on every grid.  Without the
+ * flag, grids of at most 256 tiles (14 x 14 cells a point tile, 29 x 13 a cell
+ * tile: 174 x 174 cells, 200 x 137) run a stage in one launch, in which the
+ * cell tiles form their own sources: same results bit for bit, but the times
+ * reported for such a grid are those of the two launches. */
 #define AF_FLAG_KERNEL_TIMING 4u
 
 /* Time-step reduction fused into the epilogue of a step's last stage:
