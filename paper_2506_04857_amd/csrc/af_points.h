@@ -77,8 +77,8 @@ __device__ __forceinline__ double jump2(const double a[NV], const double b[NV]) 
 // lines need of each point: 1/rho, total pressure, pressure and c_f in the
 // direction of the lines in flight (both directions for V and the centre).
 // point_exchange: where the vertical lines' part of the vertex accumulators
-// goes to the other group, on fields that are read no more by then; LIST_: the
-// tile's list of points to limit, on the last of them after that.
+// goes to the other group, on fields that are read no more by then; after that
+// LIST_, the tile's list of points, and QXY_, QYX_ (look_listed) on three of them.
 constexpr int SV_ = 0, SX_ = 8, SY_ = 16, SC_ = SV_;
 constexpr int QV_ = 24, QX_ = 29, QY_ = 33, QC_ = QV_;  // (1/rho, p_t, p, c_f[, c_f in y])
 constexpr int POINT_FIELDS = 40;
@@ -128,7 +128,8 @@ __device__ __forceinline__ void list_point(double (*s)[PB][PB], PointEnd end, in
 //           1: V finished with group 0's part of it
 //   records 0: centre;                       1: X in x, Y in y
 //   lines   0: c, X finished;                1: d, Y finished
-//   end     points listed for their limiter, four lanes a point
+//   end     listed points: limiter, four lanes a point; LLF states to be counted,
+//           a lane each where they are many
 // What bounds it is latency: dependent FP64 chains (reciprocals, square
 // roots), LDS reads and barriers, so waves in flight decide.  Two groups that
 // share one tile's LDS give four waves per SIMD at 80 KB per workgroup (two
