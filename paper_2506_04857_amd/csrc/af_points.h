@@ -44,9 +44,9 @@ __device__ __forceinline__ void acc_zero(PointAcc& P) {
 // admissible for its limiter, any other for the count of LLF states outside G,
 // the only thing that its LLF state decides (both of the limiter's bounds are at
 // most 1e-13).  The bound costs a line about 30 instructions where its two LLF
-// fluxes cost 130 (3497 -> 2552 VALU instructions per thread of the tile); at CFL
-// 0.2 smooth flow stays near 0.4, above CFL 0.45 most points of a grid can fail
-// it.
+// fluxes cost 130 (a tile of the blast 1024^2 issues 11.0 thousand wave
+// instructions, where it took 14.0 with every LLF flux formed); at CFL 0.2 smooth
+// flow stays near 0.4, above CFL 0.45 most points of a grid can fail it.
 constexpr double LLF_BOUND = 0.9, LLF_MIN = 2e-12, LLF_EMAX = 5e11;
 
 // One direction's term for a point: vc, llf_speeds of the three states; jump,
